@@ -155,7 +155,13 @@ typedef struct sv_op {
     const double* matrix;         /* SV_MATRIX only: host complex128 2^k x 2^k */
 } sv_op;
 
-/* Apply a gate list in order (each op as sv_apply_gate would).
+/* Apply a gate list in order (each op as sv_apply_gate would). From four
+ * qubits on, a sweep of the state takes as many of the gates as fit its
+ * tiles (2^12 amplitudes held in LDS; controls and phases may be on any
+ * qubit): gates that commute may change places, each is still applied on its
+ * own in FP32. A gate that no other can share a sweep with runs as in
+ * sv_apply_gate. Queues kernels only (no upload, no allocation on the
+ * device), so it can be captured.
  *   params: host doubles; row r of the batch reads
  *     params[r * params_batch_stride + op.param[j]] (stride 0 = shared).
  *   n_params: length of one row of params (indices are checked against it).

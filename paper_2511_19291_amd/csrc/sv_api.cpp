@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "sv_internal.h"
+#include "tile.h"
 
 namespace sv {
 
@@ -564,19 +565,36 @@ sv_status sv_run(sv_state s, const sv_op* ops, int n_ops, const double* params, 
         std::vector<OpInfo> info(n_ops);
         for (int i = 0; i < n_ops; ++i) info[i] = check_op(s->n, ops[i], n_params);
         const bool per_row = params_batch_stride != 0 && s->batch > 1;
-        for (int i = 0; i < n_ops; ++i) {
+        auto rows_differ = [&](int i) {
+            return per_row && info[i].np > 0 &&
+                   !same_params_all_rows(ops[i], info[i], params, params_batch_stride, s->batch);
+        };
+        auto one_gate = [&](int i) {
             const sv_op& op = ops[i];
             cd m[16];
-            if (!per_row || info[i].np == 0 || same_params_all_rows(op, info[i], params, params_batch_stride, s->batch)) {
+            if (!rows_differ(i)) {
                 op_matrix(op, info[i], params, m);
                 dispatch(all_rows(s), info[i].k, op.targets, op.n_controls, op.controls, m, s->stream);
-            } else {
-                for (int r = 0; r < s->batch; ++r) {
-                    op_matrix(op, info[i], params + r * params_batch_stride, m);
-                    dispatch(one_row(s, s->psi, r), info[i].k, op.targets, op.n_controls, op.controls, m, s->stream);
-                }
+                return;
             }
+            for (int r = 0; r < s->batch; ++r) {
+                op_matrix(op, info[i], params + r * params_batch_stride, m);
+                dispatch(one_row(s, s->psi, r), info[i].k, op.targets, op.n_controls, op.controls, m, s->stream);
+            }
+        };
+        if (n_ops < 2 || !tile_applies(s->n)) {
+            for (int i = 0; i < n_ops; ++i) one_gate(i);
+            return;
         }
+        TileList list;
+        std::vector<cd> ms;
+        for (int i = 0; i < n_ops; ++i) {
+            const int nm = rows_differ(i) ? s->batch : 1, DD = 1 << (2 * info[i].k);
+            ms.resize((size_t)nm * DD);
+            for (int r = 0; r < nm; ++r) op_matrix(ops[i], info[i], params + r * params_batch_stride, &ms[(size_t)r * DD]);
+            tile_append(list, info[i].k, ops[i].targets, ops[i].n_controls, ops[i].controls, ms.data(), nm, i);
+        }
+        tile_run(all_rows(s), s->n, list, s->stream, one_gate);
     });
 }
 
