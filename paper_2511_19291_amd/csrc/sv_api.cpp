@@ -350,6 +350,19 @@ bool z_only_terms(const sv_pauli_term* obs, int n_obs)
     return n_obs > 0;
 }
 
+void ensure_dterms(sv_state s, size_t bytes)
+{
+    if (bytes <= s->dterms_cap) return;
+    if (s->dterms) {
+        SV_HIP(hipStreamSynchronize(s->stream));
+        SV_HIP(hipFree(s->dterms));
+        s->dterms = nullptr;
+        s->dterms_cap = 0;
+    }
+    SV_HIP(hipMalloc(&s->dterms, bytes));
+    s->dterms_cap = bytes;
+}
+
 void upload_terms(sv_state s, const sv_pauli_term* obs, int n_obs, const double* coeff_rows, int rows,
                   PauliTermDev** out, const double** dcoeff)
 {
@@ -367,16 +380,7 @@ void upload_terms(sv_state s, const sv_pauli_term* obs, int n_obs, const double*
     const size_t tbytes = (t.size() * sizeof(PauliTermDev) + 15) & ~size_t(15);
     const size_t cbytes = coeff_rows ? (size_t)rows * n_obs * sizeof(double) : 0;
     const size_t bytes = tbytes + cbytes;
-    if (bytes > s->dterms_cap) {
-        if (s->dterms) {
-            SV_HIP(hipStreamSynchronize(s->stream));
-            SV_HIP(hipFree(s->dterms));
-            s->dterms = nullptr;
-            s->dterms_cap = 0;
-        }
-        SV_HIP(hipMalloc(&s->dterms, bytes));
-        s->dterms_cap = bytes;
-    }
+    ensure_dterms(s, bytes);
     unsigned char* d = static_cast<unsigned char*>(s->dterms);
     SV_HIP(hipMemcpyAsync(d, t.data(), t.size() * sizeof(PauliTermDev), hipMemcpyHostToDevice, s->stream));
     if (coeff_rows) SV_HIP(hipMemcpyAsync(d + tbytes, coeff_rows, cbytes, hipMemcpyHostToDevice, s->stream));
@@ -678,6 +682,103 @@ sv_status sv_expval_pauli(sv_state s, const sv_pauli_term* terms, int n_terms, d
 
 namespace {
 
+// The per-gate backward of a state that fits one workgroup's LDS with its
+// co-state (4..12 qubits, every parameterised gate on one target): the gate
+// list as one program per row (k_tile_adj), the loss and the drift with it.
+void adjoint_tile(sv_state s, const sv_op* ops, const std::vector<OpInfo>& info, const double* params,
+                  int64_t params_batch_stride, int n_params, const sv_pauli_term* obs, int n_obs,
+                  const double* coeff_rows, float2* lam, double* grad_out, double* loss_out, double* drift_out,
+                  const double* diag_w)
+{
+    const int B = s->batch, n_ops = (int)info.size();
+    const bool per_row = params_batch_stride != 0 && B > 1;
+    TileList list;
+    std::vector<cd> ms;
+    for (int i = n_ops - 1; i >= 0; --i) {
+        const sv_op& op = ops[i];
+        const int k = info[i].k, DD = 1 << (2 * k);
+        const int nm = per_row && info[i].np > 0 && !same_params_all_rows(op, info[i], params, params_batch_stride, B) ? B : 1;
+        ms.resize((size_t)nm * DD);
+        for (int r = 0; r < nm; ++r) {
+            cd m[16];
+            op_matrix(op, info[i], params + r * params_batch_stride, m);
+            dagger(k, m, &ms[(size_t)r * DD]);
+        }
+        const int deriv = info[i].np == 0       ? TD_NONE
+                          : op.kind == SV_RX    ? TD_X
+                          : op.kind == SV_RY    ? TD_Y
+                          : op.kind == SV_RZ    ? TD_Z
+                                                : TD_GENERAL;
+        tile_append(list, k, op.targets, op.n_controls, op.controls, ms.data(), nm, i, deriv);
+    }
+    const int nv = tile_values(list);
+    const uint64_t per = (uint64_t)nv + 2;
+    ensure_dout(s, per * B);
+    const Rows prow{s->psi, s->psi, B, B, s->N}, lrow{lam, lam, B, B, s->N};
+    const double* dcoeff = nullptr;
+    int coeff_stride = 0;
+    if (diag_w) {
+        launch_diag_lambda(prow, lrow, s->n, diag_w, s->stream);
+    } else if (z_only_terms(obs, n_obs)) {
+        // sum_t c_t Z_q(t) as one coefficient per qubit (and row)
+        const int rows = coeff_rows ? B : 1;
+        ensure_hstage(s, (uint64_t)rows * s->n * 2);
+        double* h = reinterpret_cast<double*>(s->hstage);
+        std::fill(h, h + (size_t)rows * s->n, 0.0);
+        for (int r = 0; r < rows; ++r)
+            for (int t = 0; t < n_obs; ++t)
+                h[(size_t)r * s->n + __builtin_ctzll(obs[t].z_mask)] +=
+                    coeff_rows ? coeff_rows[(size_t)r * n_obs + t] : obs[t].coeff;
+        const size_t bytes = (size_t)rows * s->n * sizeof(double);
+        ensure_dterms(s, bytes);
+        SV_HIP(hipMemcpyAsync(s->dterms, h, bytes, hipMemcpyHostToDevice, s->stream));
+        dcoeff = static_cast<const double*>(s->dterms);
+        coeff_stride = coeff_rows ? s->n : 0;
+    } else {
+        PauliTermDev* dterms = nullptr;
+        const double* dc = nullptr;
+        upload_terms(s, obs, n_obs, coeff_rows, B, &dterms, &dc);
+        launch_apply_pauli_sum(prow, lrow, s->n, dterms, n_obs, dc, s->stream, false);
+    }
+    std::vector<int> order;
+    tile_adjoint(s->psi, lam, s->n, B, list, dcoeff, coeff_stride, s->dout, order, s->stream);
+    fetch(s, per * B);
+    if (n_params > 0) std::fill(grad_out, grad_out + (size_t)B * n_params, 0.0);
+    for (int r = 0; r < B; ++r) {
+        const double* v = s->hout + per * r;
+        const double* prm_row = params + (per_row ? r * params_batch_stride : 0);
+        double* g = grad_out + (size_t)r * n_params;
+        for (int gi : order) {
+            const TileGate& tg = list.gates[gi];
+            const sv_op& op = ops[tg.op];
+            if (tg.deriv != TD_GENERAL) {
+                g[op.param[0]] += *v++;
+                continue;
+            }
+            double prm[3];
+            op_params(op, info[tg.op], prm_row, prm);
+            cd m[16], md[16], dm[16];
+            kind_matrix(op.kind, prm, m);
+            dagger(1, m, md);
+            for (int d = 0; d < info[tg.op].np; ++d) {
+                kind_dmatrix(op.kind, prm, d, dm);
+                double re = 0.0;
+                for (int a = 0; a < 2; ++a)
+                    for (int b = 0; b < 2; ++b) {
+                        const cd G = dm[a * 2] * md[b] + dm[a * 2 + 1] * md[2 + b];
+                        const double* S = v + 2 * (2 * a + b);
+                        re += G.real() * S[0] - G.imag() * S[1];
+                    }
+                g[op.param[d]] += 2.0 * re;
+            }
+            v += 8;
+        }
+        const double* tail = s->hout + per * r + nv;
+        if (loss_out) loss_out[r] = tail[0];
+        if (drift_out) drift_out[r] = std::sqrt(std::max(0.0, tail[1]));
+    }
+}
+
 sv_status adjoint_impl(sv_state s, const sv_op* ops, int n_ops, const double* params, int64_t params_batch_stride,
                        int n_params, const sv_pauli_term* obs, int n_obs, const double* coeff_rows,
                        void* lambda_buffer, double* grad_out, double* loss_out, double* drift_out,
@@ -698,6 +799,13 @@ sv_status adjoint_impl(sv_state s, const sv_op* ops, int n_ops, const double* pa
         const bool per_row = params_batch_stride != 0 && B > 1;
         float2* lam = nullptr;
         ensure_lambda(s, lambda_buffer, &lam);
+        bool one_target = n_ops > 0 && tile_adjoint_applies(s->n);
+        for (int i = 0; i < n_ops; ++i) one_target = one_target && (info[i].np == 0 || info[i].k == 1);
+        if (one_target) {
+            adjoint_tile(s, ops, info, params, params_batch_stride, n_params, obs, n_obs, coeff_rows, lam, grad_out,
+                         loss_out, drift_out, diag_w);
+            return;
+        }
         PauliTermDev* dterms = nullptr;
         const double* dcoeff = nullptr;
         if (!diag_w) upload_terms(s, obs, n_obs, coeff_rows, B, &dterms, &dcoeff);

@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <array>
 #include <cstring>
+#include <functional>
 
 #include "tile.h"
 
@@ -40,6 +41,8 @@ public:
             const TileGate& g = l.gates[ids[i]];
             Use& u = use_[i];
             const bool diag = g.kind == TK_DIAG1 || g.kind == TK_DIAG2;
+            // a derivative is formed on register amplitudes
+            if (g.deriv) u.need |= 1ull << g.targets[0];
             u.map = g.kind == TK_MAP;
             auto add = [&](int q, bool z) {
                 if (start_[q].empty() || !(z && last_z[q])) {
@@ -226,7 +229,8 @@ int tile_bits(int n) { return std::min(n, kTileMaxBits); }
 
 bool tile_applies(int n) { return n >= kTileRegBits; }
 
-void tile_append(TileList& l, int k, const int* targets, int nc, const int* controls, const cd* ms, int nm, int op)
+void tile_append(TileList& l, int k, const int* targets, int nc, const int* controls, const cd* ms, int nm, int op,
+                 int deriv)
 {
     const int D = 1 << k;
     bool diag = true, ident = true, ones = true, sign = true, exch = true, real = true, imoff = true;
@@ -246,8 +250,12 @@ void tile_append(TileList& l, int k, const int* targets, int nc, const int* cont
                 if (i == j ? v.imag() != 0.0 : v.real() != 0.0) imoff = false;
             }
     }
-    if (ident) return;
+    if (ident && !deriv) return;
+    // the generator decides what a gate with a derivative commutes with, also
+    // where its matrix is the identity
+    if (deriv && deriv != TD_Z) diag = false;
     TileGate g{};
+    g.deriv = deriv;
     g.k = k;
     for (int j = 0; j < k; ++j) g.targets[j] = targets[j];
     g.nc = nc;
@@ -255,13 +263,13 @@ void tile_append(TileList& l, int k, const int* targets, int nc, const int* cont
     g.op = op;
     g.mat = (int)l.pool.size();
     g.per_row = nm > 1;
-    if (diag && ones) {
+    if (diag && ones && !deriv) {
         for (int j = 0; j < k; ++j) g.controls[g.nc++] = targets[j];
         g.k = 0;
         g.kind = sign ? TK_SIGN : TK_ONES;
-    } else if (diag) {
+    } else if (diag && !(deriv && nc > 0)) {
         g.kind = k == 1 ? TK_DIAG1 : TK_DIAG2;
-    } else if (exch && nc <= 2 - k) {
+    } else if (exch && nc <= 2 - k && !deriv) {
         g.kind = TK_MAP;
     } else if (k == 2) {
         g.kind = TK_DENSE2;
@@ -439,11 +447,16 @@ struct Round {
     int reg_index(int tile_bit) const { return __builtin_popcount(reg_mask & ((1u << tile_bit) - 1)); }
 };
 
+int value_count(const TileGate& g) { return g.deriv == TD_NONE ? 0 : g.deriv == TD_GENERAL ? 8 : 1; }
+
 // Collects rounds until the kernel arguments are full, then launches.
 class Emitter {
 public:
-    Emitter(const Rows& rows, int n, const TileList& l, uint64_t S, int R, hipStream_t st)
-        : rows_(rows), l_(l), pl_(n, S), R_(R), st_(st), min_rows_(std::min(rows.nrows, kMinRows))
+    // launch(args, rows, derivative gates in the order of their values, last)
+    using Launch = std::function<void(const TileArgs&, int, const std::vector<int>&, bool)>;
+
+    Emitter(const Rows& rows, int n, const TileList& l, uint64_t S, int R, Launch launch)
+        : rows_(rows), l_(l), pl_(n, S), R_(R), launch_(std::move(launch)), min_rows_(std::min(rows.nrows, kMinRows))
     {
         std::memset(&a_, 0, sizeof(a_));
         a_.p0 = rows.p0;
@@ -479,19 +492,19 @@ public:
         prog_ += words;
     }
 
-    void flush()
+    void flush(bool last = false)
     {
-        if (prog_ == 0) return;
+        if (prog_ == 0 && !last) return;
         int rows_per = std::min(rows_.nrows, kMaxRows);
         if (per_row_) rows_per = std::min(rows_per, (kTileWords - prog_ - shared_) / per_row_);
         for (int r0 = 0; r0 < rows_.nrows; r0 += rows_per) {
             const int nr = std::min(rows_per, rows_.nrows - r0);
             fill(r0, nr);
             a_.row0 = r0;
-            launch_tile(a_, nr, R_, st_);
+            launch_(a_, nr, values_, last);
         }
         rounds_.clear();
-        prog_ = shared_ = per_row_ = 0;
+        prog_ = shared_ = per_row_ = nvalues_ = 0;
     }
 
 private:
@@ -625,6 +638,8 @@ private:
         Entry& e = rounds_.back();
         const int mw = kMatFloats[g.kind];
         const int words = g.per_row ? mw * min_rows_ : mw;
+        const int values = value_count(g);
+        if (nvalues_ + values > kAdjValues) return false;
         if (g.kind <= TK_DIAG1 && g.nc == 0 && in_registers(e.r, g.targets[0])) {
             const int b = e.r.reg_index(pl_.tile_bit[g.targets[0]]);
             int at = e.last[b] + 1;
@@ -656,6 +671,7 @@ private:
             prog_ += kTileHeadWords;
         }
         (g.per_row ? per_row_ : shared_) += mw;
+        nvalues_ += values;
         return true;
     }
 
@@ -663,6 +679,7 @@ private:
     {
         int pc = 0, mat = prog_;
         a_.nrounds = (int)rounds_.size();
+        values_.clear();
         for (const Entry& e : rounds_) {
             uint32_t* rw = a_.words + pc;
             e.r.words((int)e.steps.size(), rw);
@@ -707,10 +724,13 @@ private:
                         }
                     h[2] = s.per_row ? (uint32_t)stride : 0u;
                     h[3] = 0;
+                    for (int b = 0; b < R_; ++b)
+                        if (s.gate[b] >= 0 && l_.gates[s.gate[b]].deriv) derivative(s.gate[b], b, h);
                 } else {
                     const TileGate& g = l_.gates[s.gate[0]];
                     stride = kMatFloats[g.kind];
                     header(e.r, g, h);
+                    if (g.deriv) derivative(s.gate[0], __builtin_ctz(h[3]), h);
                     // the last of consecutive sign flips applies them
                     if (sign && !(h[0] & TF_SIGN)) sign[0] |= TF_APPLY;
                     sign = h[0] & TF_SIGN ? h : nullptr;
@@ -723,6 +743,13 @@ private:
             if (sign) sign[0] |= TF_APPLY;
         }
         a_.nwords = mat;
+    }
+
+    void derivative(int gi, int bit, uint32_t* h)
+    {
+        h[0] |= TF_DERIV;
+        h[3] |= (uint32_t)l_.gates[gi].deriv << (8 + 4 * bit);
+        values_.push_back(gi);
     }
 
     void header(const Round& rd, const TileGate& g, uint32_t* h) const
@@ -787,40 +814,33 @@ private:
     const TileList& l_;
     Places pl_;
     int R_;
-    hipStream_t st_;
+    Launch launch_;
     int min_rows_;
     TileArgs a_;
     std::vector<Entry> rounds_;
     std::vector<std::pair<int, int>> order_;
-    int prog_ = 0, shared_ = 0, per_row_ = 0;
+    std::vector<int> values_;         // gates with derivatives, in the order of their values
+    int prog_ = 0, shared_ = 0, per_row_ = 0, nvalues_ = 0;
 };
 
-}  // namespace
-
-void tile_sweep(const Rows& rows, int n, const TileList& l, const TileSweep& s, hipStream_t st)
+// The gates (positions in the list) of a sweep over the qubits S as rounds.
+void emit_rounds(Emitter& em, int n, const TileList& l, const std::vector<int>& gates, uint64_t S, int R)
 {
-    // Few workgroups: half as many amplitudes per thread, so that a compute unit
-    // holds twice the waves of its one or two tiles (20-qubit brickwork,
-    // one tile per unit: 24.8 us a sweep instead of 26.4; 27 qubits: 1043
-    // instead of 904, from the rounds over three bits instead of four).
-    const uint64_t groups = (1ull << (n - tile_bits(n))) * rows.nrows;
-    const int R = groups <= 2 * (uint64_t)device_info().cu_count ? kTileRegBits - 1 : kTileRegBits;
-    Frontier f(l, s.gates, n);
-    Emitter em(rows, n, l, s.qubits, R, st);
+    Frontier f(l, gates, n);
     std::vector<int> at, maps, carry, now, later;
     while (f.left() > 0) {
         at.clear();
         const uint64_t regs = f.grow(0, R, at, Frontier::kNoMaps, kRoundOptions);
         const size_t local = at.size();
-        f.take(s.qubits, at, Frontier::kMaps);
+        f.take(S, at, Frontier::kMaps);
         maps.clear();
         uint64_t changed = 0;         // qubits that a later gate changes
         for (size_t i = local; i < at.size(); ++i) {
-            maps.push_back(s.gates[at[i]]);
+            maps.push_back(gates[at[i]]);
             for (int j = 0; j < l.gates[maps.back()].k; ++j) changed |= 1ull << l.gates[maps.back()].targets[j];
         }
         now = carry;
-        for (size_t i = 0; i < local; ++i) now.push_back(s.gates[at[i]]);
+        for (size_t i = 0; i < local; ++i) now.push_back(gates[at[i]]);
         // A phase on register qubits that nothing behind it in the round waits
         // for is left to the next round, where its qubits are the threads' and
         // it costs one operation instead of one per amplitude.
@@ -831,7 +851,7 @@ void tile_sweep(const Rows& rows, int n, const TileList& l, const TileSweep& s, 
                 const TileGate& g = l.gates[now[i]];
                 uint64_t qs = 0;
                 for (int j = 0; j < g.k; ++j) qs |= 1ull << g.targets[j];
-                if (g.kind < TK_DIAG1 || g.kind > TK_SIGN) {
+                if (g.kind < TK_DIAG1 || g.kind > TK_SIGN || g.deriv) {
                     changed |= qs;
                     continue;
                 }
@@ -846,7 +866,68 @@ void tile_sweep(const Rows& rows, int n, const TileList& l, const TileSweep& s, 
         }
         em.round(regs, now, maps);
     }
+}
+
+}  // namespace
+
+void tile_sweep(const Rows& rows, int n, const TileList& l, const TileSweep& s, hipStream_t st)
+{
+    // Few workgroups: half as many amplitudes per thread, so that a compute unit
+    // holds twice the waves of its one or two tiles (20-qubit brickwork,
+    // one tile per unit: 24.8 us a sweep instead of 26.4; 27 qubits: 1043
+    // instead of 904, from the rounds over three bits instead of four).
+    const uint64_t groups = (1ull << (n - tile_bits(n))) * rows.nrows;
+    const int R = groups <= 2 * (uint64_t)device_info().cu_count ? kTileRegBits - 1 : kTileRegBits;
+    Emitter em(rows, n, l, s.qubits, R,
+               [&](const TileArgs& a, int nr, const std::vector<int>&, bool) { launch_tile(a, nr, R, st); });
+    emit_rounds(em, n, l, s.gates, s.qubits, R);
     em.flush();
+}
+
+bool tile_adjoint_applies(int n) { return n >= kTileRegBits && n <= kTileMaxBits; }
+
+int tile_values(const TileList& l)
+{
+    int v = 0;
+    for (const TileGate& g : l.gates) v += value_count(g);
+    return v;
+}
+
+void tile_adjoint(float2* psi, float2* lam, int n, int rows, const TileList& l, const double* coeff, int coeff_stride,
+                  double* out, std::vector<int>& order, hipStream_t st)
+{
+    constexpr int R = kTileRegBits - 1;
+    TileAdjArgs a{};
+    a.psi = psi;
+    a.lam = lam;
+    a.coeff = coeff;
+    a.coeff_stride = coeff_stride;
+    a.out = out;
+    a.out_stride = tile_values(l) + 2;
+    a.T = n;
+    a.first = 1;
+    order.clear();
+    const Rows rr{psi, psi, rows, rows, 1ull << n};
+    const uint64_t S = (1ull << n) - 1;
+    Emitter em(rr, n, l, S, R, [&](const TileArgs& t, int nr, const std::vector<int>& gates, bool last) {
+        a.row0 = t.row0;
+        a.nrounds = t.nrounds;
+        a.nwords = t.nwords;
+        a.nvalues = 0;
+        for (int gi : gates) a.nvalues += value_count(l.gates[gi]);
+        a.last = last;
+        std::memcpy(a.words, t.words, sizeof(a.words));
+        launch_tile_adj(a, nr, st);
+        if (t.row0 + nr < rows) return;
+        order.insert(order.end(), gates.begin(), gates.end());
+        a.value0 += a.nvalues;
+        a.first = 0;
+        a.coeff = nullptr;            // lambda lies in memory from here on
+    });
+    std::vector<int> all(l.gates.size());
+    for (size_t i = 0; i < all.size(); ++i) all[i] = (int)i;
+    emit_rounds(em, n, l, all, S, R);
+    em.flush(true);
 }
 
 }  // namespace sv

@@ -52,6 +52,17 @@ enum TileFlag : uint32_t {
     TF_DENSE2 = 16,
     TF_APPLY = 32,     // with SIGN: the last of consecutive ones
     TF_LANE_SIGN = 64, // with thread controls
+    TF_DERIV = 1u << 28,   // adjoint: the step has derivatives
+};
+
+// Derivative of a gate (adjoint): of exp(-i theta P / 2), one value; of any
+// other one-target gate, the eight parts of its pairs' correlation.
+enum TileDeriv : int {
+    TD_NONE = 0,
+    TD_X = 1,
+    TD_Y = 2,
+    TD_Z = 4,
+    TD_GENERAL = 8,
 };
 
 // Program: per round a record, then its steps, each a header of
@@ -77,6 +88,8 @@ constexpr int kTileHeadWords = 4;
 //   << 16; [3] SIGN: a bit for each register amplitude to flip; PHASE: free bits: position 0 | position 1 << 8 | their number
 //   << 16 | places << 20, 22; CTRL: the target's register bit as a mask;
 //   DENSE2: 1 << the pair's place in (1,0) (2,0) (2,1) (3,0) (3,1) (3,2)
+// with TF_DERIV (layers, CTRL): [3] |= TileDeriv of the gate on register bit b
+//   << 8 + 4 b; the values follow each other in the order of the bits
 constexpr int kPlaceReg = 0, kPlaceThread = 1, kPlaceOuter = 2;
 
 struct TileArgs {
@@ -103,6 +116,28 @@ constexpr uint32_t kTileSwz[8] = {3, 5, 9, 6, 10, 12, 7, 11};
 
 void launch_tile(const TileArgs& a, int rows, int reg_bits, hipStream_t st);
 
+// The adjoint of a state of at most kTileMaxBits qubits: rows [row0, row0 +
+// grid), a tile each.
+constexpr int kAdjValues = 256;       // derivative values of a launch
+struct TileAdjArgs {
+    float2* psi;
+    float2* lam;
+    const double* coeff;              // NULL: lambda is loaded; else lambda = sum_q coeff[row][q] Z_q psi
+    double* out;                      // per row: the values, then loss, drift
+    int64_t out_stride;
+    int coeff_stride;
+    int row0;
+    int T;
+    int nrounds;
+    int nwords;
+    int value0;                       // first value of this launch
+    int nvalues;
+    int first, last;                  // writes the loss, the drift
+    uint32_t words[kTileWords + kTilePad];
+};
+static_assert(sizeof(TileAdjArgs) <= 4096 - 128, "kernel arguments stay within 4 KiB");
+void launch_tile_adj(const TileAdjArgs& a, int rows, hipStream_t st);
+
 // One gate as the planner sees it. Fixed qubits (`nc` of them) must be 1 for
 // the gate to act: the controls, and the targets of a phase on the all-ones
 // pattern.
@@ -114,6 +149,7 @@ struct TileGate {
     int controls[SV_MAX_CONTROLS + 2];
     int mat;                          // first float of row 0's matrix in the pool
     bool per_row;                     // one matrix per row, one after the other
+    int deriv;                        // TileDeriv
     int op;                           // the caller's index of the gate
 };
 
@@ -124,8 +160,10 @@ struct TileList {
 };
 
 // Append (matrices, targets, controls): `ms` holds nm matrices of 4^k entries
-// (nm = 1, or one per row). Nothing is appended when all are the identity.
-void tile_append(TileList& l, int k, const int* targets, int nc, const int* controls, const cd* ms, int nm, int op);
+// (nm = 1, or one per row). Nothing is appended when all are the identity and
+// there is no derivative.
+void tile_append(TileList& l, int k, const int* targets, int nc, const int* controls, const cd* ms, int nm, int op,
+                 int deriv = TD_NONE);
 
 // Apply the list to every row, asynchronously on `st`. Gates that a sweep of
 // their own serves better are handed to one_gate(op).
@@ -150,6 +188,15 @@ struct TilePlannerHandle {
     bool next(TileSweep& s);
 };
 void tile_sweep(const Rows& rows, int n, const TileList& l, const TileSweep& s, hipStream_t st);
+
+// The adjoint of a list (the circuit's U^* from last to first, derivatives
+// marked) on states of 4..12 qubits: queues the launches that write every
+// row's values, loss and drift to out. `order` receives the gates (positions
+// in the list) whose values follow each other.
+bool tile_adjoint_applies(int n);
+int tile_values(const TileList& l);
+void tile_adjoint(float2* psi, float2* lam, int n, int rows, const TileList& l, const double* coeff, int coeff_stride,
+                  double* out, std::vector<int>& order, hipStream_t st);
 
 template <class F>
 void tile_run(const Rows& rows, int n, const TileList& l, hipStream_t st, const F& one_gate)

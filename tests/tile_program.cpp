@@ -181,6 +181,7 @@ static void run_tile(const TileArgs& a, int R, uint32_t tile, int y)
 }
 
 namespace sv {
+void launch_tile_adj(const TileAdjArgs&, int, hipStream_t) { std::abort(); }
 void launch_tile(const TileArgs& a, int rows, int reg_bits, hipStream_t)
 {
     ++launches;
