@@ -638,11 +638,24 @@ sv_status sv_expval_pauli(sv_state s, const sv_pauli_term* terms, int n_terms, d
         need(out != nullptr, SV_ERR_INVALID_ARGUMENT, "out is NULL");
         check_terms(s->n, terms, n_terms);
         check_not_capturing(s->stream);
-        // group terms by x mask, at most 8 per sweep
+        // strings whose x bits fit a tile, many to a sweep; of the others,
+        // those that share x, at most 8 per sweep
+        std::vector<PauliSweep> sweeps;
+        std::vector<int> rest;
+        if (pauli_tile_applies(s->n)) {
+            std::vector<uint64_t> x(n_terms), z(n_terms);
+            for (int t = 0; t < n_terms; ++t) {
+                x[t] = terms[t].x_mask;
+                z[t] = terms[t].z_mask;
+            }
+            plan_pauli_tiles(s->n, x.data(), z.data(), n_terms, sweeps, rest);
+        } else {
+            for (int t = 0; t < n_terms; ++t) rest.push_back(t);
+        }
         std::vector<PauliGroup> groups;
         std::vector<std::vector<int>> members;
         std::map<uint64_t, std::vector<int>> byx;
-        for (int t = 0; t < n_terms; ++t) byx[terms[t].x_mask].push_back(t);
+        for (int t : rest) byx[terms[t].x_mask].push_back(t);
         for (auto& kv : byx) {
             for (size_t i = 0; i < kv.second.size(); i += 8) {
                 PauliGroup g{};
@@ -659,21 +672,33 @@ sv_status sv_expval_pauli(sv_state s, const sv_pauli_term* terms, int n_terms, d
                 members.push_back(mem);
             }
         }
-        ensure_scratch(s, pauli_parts(s->n, s->batch, 8));
+        uint64_t parts = groups.empty() ? 0 : pauli_parts(s->n, s->batch, 8);
+        for (const PauliSweep& w : sweeps)
+            parts = std::max(parts, (uint64_t)s->batch * w.args.nterms * pauli_tile_grid(s->n, w.args.T));
+        ensure_scratch(s, parts);
         ensure_dout(s, (uint64_t)s->batch * n_terms);
         uint64_t off = 0;
         std::vector<uint64_t> offs;
+        for (PauliSweep& w : sweeps) {
+            w.args.p0 = w.args.p1 = s->psi;
+            w.args.nrow0 = s->batch;
+            w.args.part = s->scratch;
+            launch_pauli_tile(w.args, s->batch, s->dout + off, s->stream);
+            offs.push_back(off);
+            off += (uint64_t)s->batch * w.args.nterms;
+        }
         for (auto& g : groups) {
             offs.push_back(off);
             launch_pauli_group(all_rows(s), s->n, g, s->scratch, s->dout + off, s->stream);
             off += (uint64_t)s->batch * g.nt;
         }
         fetch(s, off);
-        for (size_t gi = 0; gi < groups.size(); ++gi)
+        for (const PauliSweep& w : sweeps) members.insert(members.begin() + (&w - sweeps.data()), w.terms);
+        for (size_t gi = 0; gi < members.size(); ++gi)
             for (int r = 0; r < s->batch; ++r)
-                for (int j = 0; j < groups[gi].nt; ++j) {
+                for (size_t j = 0; j < members[gi].size(); ++j) {
                     const int t = members[gi][j];
-                    out[(size_t)r * n_terms + t] = terms[t].coeff * s->hout[offs[gi] + (uint64_t)r * groups[gi].nt + j];
+                    out[(size_t)r * n_terms + t] = terms[t].coeff * s->hout[offs[gi] + (uint64_t)r * members[gi].size() + j];
                 }
     });
 }

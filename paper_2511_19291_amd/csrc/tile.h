@@ -138,6 +138,42 @@ struct TileAdjArgs {
 static_assert(sizeof(TileAdjArgs) <= 4096 - 128, "kernel arguments stay within 4 KiB");
 void launch_tile_adj(const TileAdjArgs& a, int rows, hipStream_t st);
 
+// Pauli strings whose x bits lie in one tile (k_pauli.hip). Words: per
+// distinct x and part [0] x (tile bits) | 1 << 12: the products' imaginary
+// part | strings << 16, then per string [0] a bit with odd z for each product
+// of a thread (16, with x 8) | z on the thread bits << 16 | 1 << 29: minus, [1] z
+// on the tile's index. The tile's bits but x's top one number the products:
+// the thread's bits, then the product's.
+constexpr int kPauliTerms = 256;      // strings of a launch
+struct PauliTileArgs {
+    const float2* p0;
+    const float2* p1;
+    uint64_t N;
+    double* part;                     // [rows][nterms][grid]
+    int nrow0;
+    int T;
+    int ngroups;
+    int nterms;
+    uint8_t pos[kTileMaxBits];
+    uint32_t words[3 * kPauliTerms];
+};
+static_assert(sizeof(PauliTileArgs) <= 4096 - 128, "kernel arguments stay within 4 KiB");
+int pauli_tile_grid(int n, int T);
+// out: [rows][nterms]
+void launch_pauli_tile(const PauliTileArgs& a, int rows, double* out, hipStream_t st);
+
+// Strings (x, z) for every row, grouped into sweeps: out receives rows *
+// (strings of the sweep) doubles per sweep, `order` the strings in that
+// order, one list per sweep. Strings it leaves out (more x bits than a tile
+// holds) are in `rest`.
+struct PauliSweep {
+    PauliTileArgs args;
+    std::vector<int> terms;
+};
+bool pauli_tile_applies(int n);
+void plan_pauli_tiles(int n, const uint64_t* x, const uint64_t* z, int count, std::vector<PauliSweep>& sweeps,
+                      std::vector<int>& rest);
+
 // One gate as the planner sees it. Fixed qubits (`nc` of them) must be 1 for
 // the gate to act: the controls, and the targets of a phase on the all-ones
 // pattern.

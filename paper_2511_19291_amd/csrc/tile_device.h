@@ -385,6 +385,27 @@ __device__ __forceinline__ RegPhase reg_phase(const u32x4& h, cword* w, uint32_t
     return r;
 }
 
+// v plus the value of another lane (0 where the mask leaves the lane out)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double plus_lane(double v)
+{
+    const uint64_t b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROWS, 0xf, false);
+    return v + __longlong_as_double((long long)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo));
+}
+
+// the wave's sum, in lane 63
+__device__ __forceinline__ double wave_sum(double v)
+{
+    v = plus_lane<0xb1, 0xf>(v);      // lane ^ 1
+    v = plus_lane<0x4e, 0xf>(v);      // lane ^ 2
+    v = plus_lane<0x141, 0xf>(v);     // mirrored within eight
+    v = plus_lane<0x140, 0xf>(v);     // mirrored within sixteen
+    v = plus_lane<0x142, 0xa>(v);     // lane 15 of a row to the next
+    return plus_lane<0x143, 0xc>(v);  // lane 31 to the upper half
+}
+
 // The lines of a program of nw words brought into the scalar cache all at
 // once: met one after the other, each would be a wait for memory.
 __device__ __forceinline__ void touch_program(cword* W, int nw)
