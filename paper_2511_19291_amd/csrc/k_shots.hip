@@ -26,6 +26,7 @@
 // matrix-free: S z = z - 2 v (v . z). One FP64 reduction sweep for T and
 // sum_b |psi_b| z_b, then one elementwise sweep.
 #include "sv_device.h"
+#include "tile_device.h"
 #include "sv_internal.h"
 
 namespace sv {
@@ -551,172 +552,269 @@ __global__ __launch_bounds__(kST) void k_gauss_y(const float2* __restrict__ psi,
 //   E_i = (1/shots) sum_b y_b s_i(b),   s_i(b) = 1 - 2 (bit i of b);
 // for F = sum_i g_i E_i, c_b = sum_i g_i s_i(b), Q = sum_b c_b u_b d_b:
 //   dF/dp_b = c_b + c_b K / (R sqrt shots)
-//             + (c_b (S z)_b + 2 z_b Q / R - 4 d_b K Q / R^2) / (2 u_b sqrt shots)
+//             + (c_b + 2 Q / R) (z_b - 2 d_b K / R) / (2 u_b sqrt shots)
 //   (that last term 0 where u_b = 0), and
-//   w_b = dF/dq_b = (dF/dp_b - sum_b' p_b' dF/dp_b') / T.
-// y is the sampler's (same formula, same rounding); every sum is FP64 in a
-// fixed order.
+//   w_b = dF/dq_b = (dF/dp_b - M) / T,  M = sum_b' p_b' dF/dp_b'.
+// u_b d_b is -p_b away from the last index, so the sums q(S) of q_b and a(S) of
+// sqrt(q_b) z_b over all b and over those with bit i set, the last index left
+// out of both, give T, R, K, every E_i, Q and M: one sweep of state and normals
+// forward, that and one that writes w backward. Every sum is FP64 in a fixed
+// order. At 26 qubits, where both sweeps are bound by memory: forward 799 us
+// (three kernels: T and K, y and its sums, their end) -> 212 us, backward 1038 us
+// (five sweeps) -> 496 us (w: 1.5 GiB in 285).
 
 struct GzArgs {
     const float2* psi;
     const double* z;
     uint64_t N;
     int n;
+    int g_rows;               // workgroups of k_gz_sums
     double shots;
     double g[SV_MAX_QUBITS];
     double G;                 // sum of g
-    const double* sc;         // [0] T, [1] r = sqrt R, [2] v . z (v = d / r), [3] Q, [4] M
-    double* part;
+    double* part;             // [2 (n + 1)][g_rows]
+    double* sums;             // [2 (n + 1)]: q with bit i set, q, a with bit i set, a
+    double* sc;               // GzScalars
+    double* est;
     double* w;
 };
 
-// y_b of the sampler
-__device__ __forceinline__ double gz_y(double q, bool lastb, double zb, const double* sc, double shots, double sq)
+// w_b = c_b cw + (c_b + cq) (z_b - kd d_b) cu / u_b - m, u_b = sqrt(q_b) ut
+struct GzScalars {
+    double cw, cq, kd, cu, ut, m;
+};
+
+// A unit is 2 amplitudes of a thread, a block kUnits units of each thread: bit
+// 0 of b is the amplitude in the unit, then 8 bits of thread, 3 of unit, and
+// the block's. q and a are kept per thread by amplitude and unit bit; a block's
+// wave sums go to the lane of each set bit of the block's index.
+constexpr int kUnits = 8;
+constexpr int kBlockBits = 12;
+static_assert(2 * kST * kUnits == 1 << kBlockBits && kST == 256, "bits of a block");
+
+struct GzAcc {
+    double all, odd, unit[3], block;
+};
+
+// the wave's value of v, which is in its lane 63
+__device__ __forceinline__ double from_last(double v)
 {
-    const double T = sc[0], r = sc[1], vz = sc[2];
-    const double p = q / T;
-    const double u = sqrt(p);
-    const double vb = r > 0.0 ? ((lastb ? 1.0 : 0.0) - u) / r : 0.0;
-    return shots * p + sq * u * (zb - 2.0 * vb * vz);
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
+                            __builtin_amdgcn_readlane(__double2loint(v), 63));
 }
 
-// c_b = G - 2 sum_{i: bit i of b} g_i from per-byte tables in LDS
-__device__ __forceinline__ double gz_c(const double (*tab)[256], int nt, double G, uint64_t b)
+__device__ __forceinline__ void gz_block(GzAcc& c, double s, uint64_t blk)
 {
-    double s = 0.0;
-    for (int j = 0; j < nt; ++j) s += tab[j][(b >> (8 * j)) & 255];
-    return G - 2.0 * s;
+    c.all += s;
+    const double w = from_last(wave_sum(s));
+    c.block += (blk >> (threadIdx.x & 63)) & 1 ? w : 0.0;
 }
 
-__device__ void gz_tables(const GzArgs& a, double (*tab)[256], int nt)
+// the workgroup's sums of one quantity: row i of `part`
+__device__ __forceinline__ void gz_rows(const GzAcc& c, int n, double (*sh)[64], double* part, int stride)
 {
-    for (int j = 0; j < nt; ++j) {
-        double s = 0.0;
-        for (int k = 0; k < 8 && 8 * j + k < a.n; ++k)
-            if ((threadIdx.x >> k) & 1) s += a.g[8 * j + k];
-        tab[j][threadIdx.x] = s;
-    }
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    double mine = 0.0;                                // lane i: bit i; lane 63: all
+    auto put = [&](int i, double v) SV_INLINE {
+        const double s = from_last(wave_sum(v));
+        if (lane == i) mine = s;
+    };
+    put(63, c.all);
+    put(0, c.odd);
+    for (int k = 0; k < 6; ++k) put(1 + k, (lane >> k) & 1 ? c.all : 0.0);
+    for (int k = 0; k < 2; ++k) put(7 + k, (w >> k) & 1 ? c.all : 0.0);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) put(9 + k, c.unit[k]);
+    const double b = __shfl(c.block, (lane - kBlockBits) & 63, 64);
+    if (lane >= kBlockBits && lane < n) mine = b;
     __syncthreads();
+    sh[w][lane] = mine;
+    __syncthreads();
+    if (w == 0 && (lane < n || lane == 63)) {
+        const double s = (sh[0][lane] + sh[1][lane]) + (sh[2][lane] + sh[3][lane]);
+        part[(size_t)(lane == 63 ? n : lane) * stride + blockIdx.x] = s;
+    }
 }
 
-// E partials: per workgroup sum_b y_b and sum_{bit i of b} y_b for every i
-__global__ __launch_bounds__(kST) void k_gz_est(GzArgs a)
+// Two units at a time and 4 waves per SIMD: the waves cover each other's
+// reads (1 GiB at 26 qubits in 201 us; 8 units at a time, 3 waves of 148
+// registers, 249; 6 waves 208, 8 waves 262).
+template <bool EDGE>
+__device__ __forceinline__ void gz_units(const GzArgs& a, uint64_t blk, GzAcc& q, GzAcc& s)
 {
-    __shared__ double sh[kST / 64];
-    const double sq = sqrt(a.shots);
-    double tot = 0.0, acc[SV_MAX_QUBITS];
-#pragma unroll
-    for (int i = 0; i < SV_MAX_QUBITS; ++i) acc[i] = 0.0;
-    for (uint64_t j = (uint64_t)blockIdx.x * kST + threadIdx.x; j < a.N / 2; j += (uint64_t)gridDim.x * kST) {
-        const float4 v = reinterpret_cast<const float4*>(a.psi)[j];
-        const double2 zz = reinterpret_cast<const double2*>(a.z)[j];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const uint64_t b = 2 * j + h;
-            const bool lastb = b == a.N - 1;
-            const double y = gz_y(prob(h ? make_float2(v.z, v.w) : make_float2(v.x, v.y)), lastb,
-                                  lastb ? 0.0 : (h ? zz.y : zz.x), a.sc, a.shots, sq);
-            tot += y;
-#pragma unroll
-            for (int i = 0; i < SV_MAX_QUBITS; ++i)
-                if (i < a.n && ((b >> i) & 1)) acc[i] += y;
+    const uint64_t end = a.N / 2 - 1;                 // the unit of the last index
+    double sq = 0.0, ss = 0.0;
+#pragma unroll 1
+    for (int k = 0; k < kUnits; k += 2) {
+        const uint64_t j0 = (blk * kUnits + k) * kST + threadIdx.x, j1 = j0 + kST;
+        const uint64_t i0 = EDGE && j0 > end ? end : j0, i1 = EDGE && j1 > end ? end : j1;
+        const float4 v0 = reinterpret_cast<const float4*>(a.psi)[i0], v1 = reinterpret_cast<const float4*>(a.psi)[i1];
+        double2 z0 = reinterpret_cast<const double2*>(a.z)[i0], z1 = reinterpret_cast<const double2*>(a.z)[i1];
+        double e0 = prob(make_float2(v0.x, v0.y)), o0 = prob(make_float2(v0.z, v0.w));
+        double e1 = prob(make_float2(v1.x, v1.y)), o1 = prob(make_float2(v1.z, v1.w));
+        if (EDGE) {
+            if (j0 > end) e0 = z0.x = 0.0;
+            if (j0 >= end) o0 = z0.y = 0.0;
+            if (j1 > end) e1 = z1.x = 0.0;
+            if (j1 >= end) o1 = z1.y = 0.0;
         }
+        auto add = [&](GzAcc& c, double& all, double w0, double x0, double w1, double x1) SV_INLINE {
+            const double t1 = w1 + x1, t = (w0 + x0) + t1;
+            c.odd += x0 + x1;
+            c.unit[0] += t1;
+            if (k & 2) c.unit[1] += t;
+            if (k & 4) c.unit[2] += t;
+            all += t;
+        };
+        add(q, sq, e0, o0, e1, o1);
+        add(s, ss, sqrt(e0) * z0.x, sqrt(o0) * z0.y, sqrt(e1) * z1.x, sqrt(o1) * z1.y);
     }
-    const int stride = a.n + 1;
-    const double st = wg_sum256(tot, sh);
-    if (threadIdx.x == 0) a.part[(size_t)blockIdx.x * stride + a.n] = st;
-#pragma unroll
-    for (int i = 0; i < SV_MAX_QUBITS; ++i) {
-        if (i < a.n) {     // uniform: every thread takes the same branches around the barriers
-            const double si = wg_sum256(acc[i], sh);
-            if (threadIdx.x == 0) a.part[(size_t)blockIdx.x * stride + i] = si;
-        }
-    }
+    gz_block(q, sq, blk);
+    gz_block(s, ss, blk);
 }
 
-// E_i = (tot - 2 acc_i) / shots from the partials, in workgroup order
-__global__ __launch_bounds__(kST) void k_gz_est_final(const double* __restrict__ part, int g, int n, double shots,
-                                                      double* __restrict__ est)
+__global__ __launch_bounds__(kST, 4) void k_gz_sums(GzArgs a)
+{
+    __shared__ double sh[kST / 64][64];
+    GzAcc q{}, s{};
+    const uint64_t blocks = (a.N + (1ull << kBlockBits) - 1) >> kBlockBits;
+    for (uint64_t blk = blockIdx.x; blk < blocks; blk += gridDim.x) {
+        if (blk == blocks - 1)
+            gz_units<true>(a, blk, q, s);
+        else
+            gz_units<false>(a, blk, q, s);
+    }
+    gz_rows(q, a.n, sh, a.part, (int)gridDim.x);
+    gz_rows(s, a.n, sh, a.part + (size_t)(a.n + 1) * gridDim.x, (int)gridDim.x);
+}
+
+__global__ __launch_bounds__(kST) void k_gz_rowsum(GzArgs a)
 {
     __shared__ double sh[kST / 64];
-    const int stride = n + 1;
-    double tv = 0.0;
-    for (int k = threadIdx.x; k < g; k += kST) tv += part[(size_t)k * stride + n];
-    const double tot = wg_sum256(tv, sh);
-    for (int i = 0; i < n; ++i) {
-        double v = 0.0;
-        for (int k = threadIdx.x; k < g; k += kST) v += part[(size_t)k * stride + i];
-        const double si = wg_sum256(v, sh);
-        if (threadIdx.x == 0) est[i] = (tot - 2.0 * si) / shots;
-    }
+    const double* p = a.part + (size_t)blockIdx.x * a.g_rows;
+    double v = 0.0;
+    for (int k = threadIdx.x; k < a.g_rows; k += kST) v += p[k];
+    const double s = wg_sum256(v, sh);
+    if (threadIdx.x == 0) a.sums[blockIdx.x] = s;
 }
 
-// Q partials: sum_b c_b u_b d_b
-__global__ __launch_bounds__(kST) void k_gz_q(GzArgs a)
+// T, u of the last index, R, K from the sums
+struct GzBase {
+    double T, ql, ul, R, K, ud;                       // ud = u d of the last index
+};
+
+__device__ __forceinline__ GzBase gz_base(const GzArgs& a)
 {
-    __shared__ double sh[kST / 64];
-    __shared__ double tab[(SV_MAX_QUBITS + 7) / 8][256];
-    const int nt = (a.n + 7) / 8;
-    gz_tables(a, tab, nt);
-    const double T = a.sc[0];
-    double acc = 0.0;
-    for (uint64_t b = (uint64_t)blockIdx.x * kST + threadIdx.x; b < a.N; b += (uint64_t)gridDim.x * kST) {
-        const double u = sqrt(prob(a.psi[b]) / T);
-        const double d = (b == a.N - 1 ? 1.0 : 0.0) - u;
-        acc += gz_c(tab, nt, a.G, b) * u * d;
-    }
-    const double s = wg_sum256(acc, sh);
-    if (threadIdx.x == 0) a.part[blockIdx.x] = s;
+    GzBase r;
+    const double rest = a.sums[a.n];
+    r.ql = prob(a.psi[a.N - 1]);
+    r.T = rest + r.ql;
+    r.ul = sqrt(r.ql / r.T);
+    const double dl = rest / r.T / (1.0 + r.ul);      // 1 - u
+    r.R = rest / r.T + dl * dl;
+    r.K = -a.sums[2 * a.n + 1] / sqrt(r.T);
+    r.ud = r.ul * dl;
+    return r;
 }
 
-// w'_b = dF/dp_b (written to w) and partials of M = sum_b p_b w'_b
+// E_i = (Y - 2 Y_i) / shots with Y(S) = shots p(S) + sqrt(shots) (u z (S) - 2 K / R u d (S))
+__global__ void k_gz_est(GzArgs a)
+{
+    const int i = threadIdx.x;
+    if (i >= a.n) return;
+    const GzBase r = gz_base(a);
+    const double sq = sqrt(a.shots), k2 = r.R > 0.0 ? 2.0 * r.K / r.R : 0.0;
+    auto y = [&](int j) SV_INLINE {
+        const double p = a.sums[j] / r.T;
+        return a.shots * (p + r.ql / r.T) + sq * (a.sums[a.n + 1 + j] / sqrt(r.T) - k2 * (r.ud - p));
+    };
+    a.est[i] = (y(a.n) - 2.0 * y(i)) / a.shots;
+}
+
+__global__ __launch_bounds__(64) void k_gz_scalars(GzArgs a)
+{
+    const int i = threadIdx.x;
+    const GzBase r = gz_base(a);
+    const double sq = sqrt(a.shots), st = sqrt(r.T);
+    const double* A = a.sums + a.n + 1;
+    // sums of c p, c u z without the last index (in lane 63)
+    double cp = wave_sum(i < a.n ? a.g[i] * (a.sums[a.n] - 2.0 * a.sums[i]) : 0.0) / r.T;
+    const double cuz = wave_sum(i < a.n ? a.g[i] * (A[a.n] - 2.0 * A[i]) : 0.0) / st;
+    const double cl = -a.G;                           // every bit of the last index is set
+    const double Q = cl * r.ud - cp;
+    cp += cl * (r.ql / r.T);
+    GzScalars o;
+    double alpha = 1.0, m;
+    if (r.R > 0.0) {
+        alpha += r.K / (r.R * sq);
+        o.cq = 2.0 * Q / r.R;
+        o.kd = 2.0 * r.K / r.R;
+        m = alpha * cp + (cuz - o.kd * Q - o.cq * r.K - o.cq * o.kd * (r.ud - a.sums[a.n] / r.T)) / (2.0 * sq);
+    } else {
+        o.cq = o.kd = 0.0;
+        m = cp + cuz / (2.0 * sq);
+    }
+    o.cw = alpha / r.T;
+    o.cu = 1.0 / (2.0 * sq * r.T);
+    o.ut = 1.0 / st;
+    o.m = m / r.T;
+    if (i == 63) *reinterpret_cast<GzScalars*>(a.sc) = o;
+}
+
+// w. c_b = G - 2 sum_{i: bit i of b} g_i: the thread's bits once, the block's by
+// byte from tables in LDS.
 __global__ __launch_bounds__(kST) void k_gz_w(GzArgs a)
 {
-    __shared__ double sh[kST / 64];
-    __shared__ double tab[(SV_MAX_QUBITS + 7) / 8][256];
-    const int nt = (a.n + 7) / 8;
-    gz_tables(a, tab, nt);
-    const double T = a.sc[0], r = a.sc[1], Q = a.sc[3];
-    const double R = r * r, K = r * a.sc[2];
-    const double sq = sqrt(a.shots);
-    double acc = 0.0;
-    for (uint64_t b = (uint64_t)blockIdx.x * kST + threadIdx.x; b < a.N; b += (uint64_t)gridDim.x * kST) {
-        const bool lastb = b == a.N - 1;
-        const double p = prob(a.psi[b]) / T;
-        const double u = sqrt(p);
-        const double d = (lastb ? 1.0 : 0.0) - u;
-        const double zb = lastb ? 0.0 : a.z[b];
-        const double c = gz_c(tab, nt, a.G, b);
-        double wp = c;
-        if (R > 0.0) {
-            const double sz = zb - 2.0 * d * K / R;
-            wp += c * K / (R * sq);
-            if (u > 0.0) wp += (c * sz + 2.0 * zb * Q / R - 4.0 * d * K * Q / (R * R)) / (2.0 * u * sq);
-        } else if (u > 0.0) {
-            wp += c * zb / (2.0 * u * sq);
-        }
-        a.w[b] = wp;
-        acc += p * wp;
+    __shared__ double tab[(SV_MAX_QUBITS - kBlockBits + 7) / 8][256];
+    const int nt = a.n > kBlockBits ? (a.n - kBlockBits + 7) / 8 : 0;
+    double mine = 0.0;
+    for (int k = 0; k < 8 && 1 + k < a.n; ++k)
+        if ((threadIdx.x >> k) & 1) mine += a.g[1 + k];
+    for (int j = 0; j < nt; ++j) {
+        double s = 0.0;
+        for (int k = 0; k < 8 && kBlockBits + 8 * j + k < a.n; ++k)
+            if ((threadIdx.x >> k) & 1) s += a.g[kBlockBits + 8 * j + k];
+        tab[j][threadIdx.x] = s;
     }
-    const double s = wg_sum256(acc, sh);
-    if (threadIdx.x == 0) a.part[blockIdx.x] = s;
-}
-
-// a scalar from g partials, in workgroup order
-__global__ __launch_bounds__(kST) void k_gz_scalar(const double* __restrict__ part, int g, double* __restrict__ out)
-{
-    __shared__ double sh[kST / 64];
-    double v = 0.0;
-    for (int k = threadIdx.x; k < g; k += kST) v += part[k];
-    const double s = wg_sum256(v, sh);
-    if (threadIdx.x == 0) *out = s;
-}
-
-__global__ __launch_bounds__(kST) void k_gz_fix(double* __restrict__ w, uint64_t N, const double* __restrict__ sc)
-{
-    const double T = sc[0], M = sc[4];
-    for (uint64_t b = (uint64_t)blockIdx.x * kST + threadIdx.x; b < N; b += (uint64_t)gridDim.x * kST)
-        w[b] = (w[b] - M) / T;
+    const double g0 = 2.0 * a.g[0], gk[3] = {a.n > 9 ? a.g[9] : 0.0, a.n > 10 ? a.g[10] : 0.0, a.n > 11 ? a.g[11] : 0.0};
+    const GzScalars sc = *reinterpret_cast<const GzScalars*>(a.sc);
+    __syncthreads();
+    const uint64_t units = a.N / 2, blocks = (a.N + (1ull << kBlockBits) - 1) >> kBlockBits;
+    for (uint64_t blk = blockIdx.x; blk < blocks; blk += gridDim.x) {
+        double cb = mine;
+        for (int j = 0; j < nt; ++j) cb += tab[j][(blk >> (8 * j)) & 255];
+#pragma unroll
+        for (int k0 = 0; k0 < kUnits; k0 += 4) {
+            float4 v[4];
+            double2 zz[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint64_t j = (blk * kUnits + k0 + k) * kST + threadIdx.x;
+                if (j < units) {
+                    v[k] = reinterpret_cast<const float4*>(a.psi)[j];
+                    zz[k] = reinterpret_cast<const double2*>(a.z)[j];
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint64_t j = (blk * kUnits + k0 + k) * kST + threadIdx.x;
+                if (j >= units) continue;
+                const double ck = cb + (k0 ? gk[2] : 0.0) + (k & 2 ? gk[1] : 0.0) + (k & 1 ? gk[0] : 0.0);
+                double out[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const bool lastb = h && j == units - 1;
+                    const double c = a.G - 2.0 * ck - (h ? g0 : 0.0);
+                    const double u = sqrt(prob(h ? make_float2(v[k].z, v[k].w) : make_float2(v[k].x, v[k].y))) * sc.ut;
+                    const double z = lastb ? 0.0 : (h ? zz[k].y : zz[k].x), d = (lastb ? 1.0 : 0.0) - u;
+                    const double f = u > 0.0 ? (c + sc.cq) * (z - sc.kd * d) * sc.cu / u : 0.0;
+                    out[h] = c * sc.cw + f - sc.m;
+                }
+                a.w[2 * j] = out[0];                  // w may be aligned to 8 bytes only
+                a.w[2 * j + 1] = out[1];
+            }
+        }
+    }
 }
 
 template <class T>
@@ -925,12 +1023,11 @@ namespace {
 
 int gz_grid(uint64_t N)
 {
-    return (int)std::max<uint64_t>(1, std::min<uint64_t>((N / 2 + kST - 1) / kST, (uint64_t)device_info().cu_count * 8));
+    return (int)std::max<uint64_t>(1, std::min<uint64_t>(N >> kBlockBits, (uint64_t)device_info().cu_count * 4));
 }
 
-// scratch: [0, 2g) T and A partials; [2g, 2g + 8) scalars; then the
-// estimate partials (g (n + 1)) or the Q / M partials (g)
-GzArgs gz_args(const GaussZLaunch& a, int g)
+// scratch: [0, 8) scalars, then the sums and their partials
+GzArgs gz_sums(const GaussZLaunch& a, hipStream_t st)
 {
     GzArgs x{};
     x.psi = a.psi;
@@ -943,58 +1040,39 @@ GzArgs gz_args(const GaussZLaunch& a, int g)
         x.g[i] = a.g[i];
         x.G += a.g[i];
     }
-    x.sc = a.scratch + 2 * g;
-    x.part = a.scratch + 2 * g + 8;
+    x.g_rows = gz_grid(x.N);
+    x.sc = a.scratch;
+    x.sums = a.scratch + 8;
+    x.part = x.sums + 2 * (a.n + 1);
+    x.est = a.est;
     x.w = a.w;
+    hipLaunchKernelGGL(k_gz_sums, dim3(x.g_rows), dim3(kST), 0, st, x);
+    SV_HIP(hipGetLastError());
+    hipLaunchKernelGGL(k_gz_rowsum, dim3(2 * (a.n + 1)), dim3(kST), 0, st, x);
+    SV_HIP(hipGetLastError());
     return x;
-}
-
-void gz_scalars(const GaussZLaunch& a, int g, hipStream_t st)
-{
-    const uint64_t N = 1ull << a.n;
-    double* part = a.scratch;
-    double* sc = a.scratch + 2 * g;
-    hipLaunchKernelGGL(k_gauss_partial, dim3(g), dim3(kST), 0, st, a.psi, a.z, N, part);
-    SV_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_gauss_final, dim3(1), dim3(kST), 0, st, a.psi, N, part, g, sc);
-    SV_HIP(hipGetLastError());
 }
 
 }  // namespace
 
 uint64_t gauss_z_scratch_doubles(int n)
 {
-    const uint64_t g = (uint64_t)device_info().cu_count * 8;
-    return 2 * g + 8 + g * (uint64_t)(n + 1) + 8;
+    return 8 + 2 * (uint64_t)(n + 1) * (1 + (uint64_t)device_info().cu_count * 4);
 }
 
 void launch_gauss_z(const GaussZLaunch& a, hipStream_t st)
 {
-    const int g = gz_grid(1ull << a.n);
-    gz_scalars(a, g, st);
-    const GzArgs x = gz_args(a, g);
-    hipLaunchKernelGGL(k_gz_est, dim3(g), dim3(kST), 0, st, x);
-    SV_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_gz_est_final, dim3(1), dim3(kST), 0, st, x.part, g, a.n, a.shots, a.est);
+    const GzArgs x = gz_sums(a, st);
+    hipLaunchKernelGGL(k_gz_est, dim3(1), dim3(64), 0, st, x);
     SV_HIP(hipGetLastError());
 }
 
 void launch_gauss_z_backward(const GaussZLaunch& a, hipStream_t st)
 {
-    const uint64_t N = 1ull << a.n;
-    const int g = gz_grid(N);
-    gz_scalars(a, g, st);
-    const GzArgs x = gz_args(a, g);
-    double* sc = a.scratch + 2 * g;
-    hipLaunchKernelGGL(k_gz_q, dim3(g), dim3(kST), 0, st, x);
+    const GzArgs x = gz_sums(a, st);
+    hipLaunchKernelGGL(k_gz_scalars, dim3(1), dim3(64), 0, st, x);
     SV_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_gz_scalar, dim3(1), dim3(kST), 0, st, x.part, g, sc + 3);
-    SV_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_gz_w, dim3(g), dim3(kST), 0, st, x);
-    SV_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_gz_scalar, dim3(1), dim3(kST), 0, st, x.part, g, sc + 4);
-    SV_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_gz_fix, dim3(g), dim3(kST), 0, st, a.w, N, x.sc);
+    hipLaunchKernelGGL(k_gz_w, dim3(x.g_rows), dim3(kST), 0, st, x);
     SV_HIP(hipGetLastError());
 }
 
