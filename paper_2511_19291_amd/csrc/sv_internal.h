@@ -277,6 +277,30 @@ struct FusedLaunch {
 };
 void launch_fused_mfma(const FusedLaunch& f, hipStream_t st);
 
+// Several blocks of at most five qubits per sweep (k_fused_tile.hip). A tile is
+// qubits 0..3 and nine more. Words of a block: [0..6] the byte addresses in LDS
+// of its bits, 16 bits each: 5 row bits (targets[0] first), 5 column bits, 3 part
+// bits; [7] its fragments' distance from amat in units of 16 bytes.
+constexpr int kFusedTileBits = 13;
+constexpr int kFusedTileBlocks = 64;  // of a launch
+constexpr int kFusedTileWords = 8;
+struct FusedTileArgs {
+    float2* psi;
+    uint64_t N;
+    const float* amat;
+    uint32_t amat_stride;     // floats between batch rows' matrices (0: one matrix for every row)
+    int nblocks;
+    uint8_t pos[16];          // qubit of each tile bit, ascending
+    uint32_t blocks[kFusedTileBlocks * kFusedTileWords];
+};
+static_assert(sizeof(FusedTileArgs) <= 4096 - 128, "kernel arguments stay within 4 KiB");
+// LDS position of tile index i (linear in its bits)
+constexpr __host__ __device__ uint32_t fused_tile_place(uint32_t i)
+{
+    return i ^ ((i >> 5) & 31u) ^ ((i >> 10) & 1u) * 15u ^ ((i >> 11) & 1u) * 27u ^ ((i >> 12) & 1u) * 30u;
+}
+void launch_fused_tile(const FusedTileArgs& a, int nrows, int mode, hipStream_t st);
+
 // Six-qubit blocks (BF16x3, all targets >= 6, 12 <= n <= 32).
 struct Fused6Launch {
     float2* psi;
