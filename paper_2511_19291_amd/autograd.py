@@ -61,16 +61,26 @@ def _check_drift(drift) -> None:
                               "the backward did not start from this forward's output")
 
 
-# The forward fuses the gates into matrix-core blocks once the state is
-# large enough for the blocks to repay their host planning: measured on one
-# MI355X, batch 16 from 20 qubits (18: 1.9 ms per-gate vs 2.8 ms fused; 20:
-# 5.9 vs 4.5) and batch 1 from 22 (20: 2.8 vs 3.9 ms; 22: 6.5 vs 5.1), i.e.
-# 2n + log2(batch) >= 44.
-FUSED_FORWARD_MIN_QUBITS = 20
+def _mostly_general(circuit) -> bool:
+    """Whether the circuit has more than a third as many general one-target
+    gates with parameters (U3, phases) as rotations."""
+    general = sum(1 for op in circuit.ops if op.params and op.kind not in ("rx", "ry", "rz"))
+    return 3 * general > sum(1 for op in circuit.ops if op.params) - general
+
+
+# The forward runs gate lists in tiles of the state (``run``), which needs no
+# planning of blocks on the host. Matrix-core blocks (``run_fused``) win only
+# where the gates are general ones and the state large: measured on one MI355X
+# with 6 layers, batch 1, rings of RX and RY at 22 / 25 / 26 qubits 0.52 /
+# 2.8 / 5.5 ms against 2.3 / 4.6 / 8.0 fused; bricks of U3 0.30 / 1.6 / 3.2
+# against 1.0 / 2.0 / 3.4, with 8 layers at 26 4.3 against 3.8.
+FUSED_FORWARD_MIN_QUBITS = 26
 
 
 def default_fuse(circuit, batch: int = 1) -> bool:
-    return 2 * circuit.n + np.log2(max(int(batch), 1)) >= 2 * FUSED_FORWARD_MIN_QUBITS + 4
+    if 2 * circuit.n + np.log2(max(int(batch), 1)) < 2 * FUSED_FORWARD_MIN_QUBITS:
+        return False
+    return _mostly_general(circuit)
 
 
 def _forward(state, circuit, p, fuse: bool) -> None:
@@ -81,20 +91,27 @@ def _forward(state, circuit, p, fuse: bool) -> None:
         state.run(circuit, params=p)
 
 
-# Backward form by width (measured on one MI355X, rings and batched ladders of
-# 10 to 28 qubits): below 13 qubits the per-gate backward (launch-bound
-# sizes), from 13 the matrix-core blocks, which from there on match or beat
-# both the per-gate and the 4-qubit VALU blocked backward. The VALU blocks stay
-# available through ``block_qubits``.
+# Backward form (measured on one MI355X, batch 1 unless said). Where every
+# parameter sits on a one-target gate the per-gate backward runs in tiles of
+# the state: rings of RX and RY (6 layers) at 13 / 18 / 22 / 26 qubits 0.43 /
+# 0.59 / 1.25 / 16.6 ms against 0.88 / 1.30 / 2.5 / 22.8 with matrix-core blocks,
+# ladders of 16 rows at 18 / 22 qubits 0.55 / 6.3 against 1.8 / 10.2. A general
+# gate costs it 2.5 times a rotation, a block the same: bricks of U3 at 18 /
+# 20 / 22 / 26 qubits 0.56 / 0.63 / 1.46 / 22.0 ms against 0.80 / 0.91 / 1.21 /
+# 9.9. The VALU blocks stay available through ``block_qubits``.
 MFMA_MIN_QUBITS = 13
+TILE_GENERAL_MAX_QUBITS = 20
 
 
-def default_block_qubits(circuit) -> int:
-    """Backward form for this circuit: ``sv.ADJOINT_MFMA`` (matrix-core
-    blocks) from 13 qubits when every gate fits in four qubits, else 0 (per
-    gate)."""
-    fits = all(len(op.targets) + len(op.controls) <= 4 for op in circuit.ops)
-    if fits and circuit.n >= MFMA_MIN_QUBITS:
+def default_block_qubits(circuit, batch: int = 1) -> int:
+    """Backward form for this circuit: 0 (per gate) below 13 qubits, where a
+    gate has more than four qubits, and where tiles serve the gates better;
+    else ``sv.ADJOINT_MFMA`` (matrix-core blocks)."""
+    if circuit.n < MFMA_MIN_QUBITS or any(len(op.targets) + len(op.controls) > 4 for op in circuit.ops):
+        return 0
+    if any(op.params and len(op.targets) > 1 for op in circuit.ops):
+        return sv.ADJOINT_MFMA
+    if circuit.n + np.log2(max(int(batch), 1)) > TILE_GENERAL_MAX_QUBITS and _mostly_general(circuit):
         return sv.ADJOINT_MFMA
     return 0
 
@@ -137,7 +154,7 @@ class QuantumExpval(torch.nn.Module):
         self.circuit = circuit
         self.terms = list(terms)
         self.state = sv.State(circuit.n, batch, device=device)
-        self.block_qubits = default_block_qubits(circuit) if block_qubits is None else block_qubits
+        self.block_qubits = default_block_qubits(circuit, batch) if block_qubits is None else block_qubits
         self.fuse = default_fuse(circuit, batch) if fuse is None else bool(fuse)
 
     def forward(self, params: torch.Tensor) -> torch.Tensor:
@@ -186,7 +203,7 @@ class MeasureAllZ(torch.nn.Module):
         super().__init__()
         self.circuit = circuit
         self.state = sv.State(circuit.n, batch, device=device)
-        self.block_qubits = default_block_qubits(circuit) if block_qubits is None else block_qubits
+        self.block_qubits = default_block_qubits(circuit, batch) if block_qubits is None else block_qubits
         self.fuse = default_fuse(circuit, batch) if fuse is None else bool(fuse)
 
     def forward(self, params: torch.Tensor) -> torch.Tensor:

@@ -707,9 +707,9 @@ sv_status sv_expval_pauli(sv_state s, const sv_pauli_term* terms, int n_terms, d
 
 namespace {
 
-// The per-gate backward of a state that fits one workgroup's LDS with its
-// co-state (4..12 qubits, every parameterised gate on one target): the gate
-// list as one program per row (k_tile_adj), the loss and the drift with it.
+// The per-gate backward in tiles (4 qubits and more, every parameterised gate on
+// one target): up to 12 qubits the gate list as one program per row, the loss
+// and the drift with it; above, a program per sweep.
 void adjoint_tile(sv_state s, const sv_op* ops, const std::vector<OpInfo>& info, const double* params,
                   int64_t params_batch_stride, int n_params, const sv_pauli_term* obs, int n_obs,
                   const double* coeff_rows, float2* lam, double* grad_out, double* loss_out, double* drift_out,
@@ -737,9 +737,87 @@ void adjoint_tile(sv_state s, const sv_op* ops, const std::vector<OpInfo>& info,
         tile_append(list, k, op.targets, op.n_controls, op.controls, ms.data(), nm, i, deriv);
     }
     const int nv = tile_values(list);
+    const Rows prow{s->psi, s->psi, B, B, s->N}, lrow{lam, lam, B, B, s->N};
+    if (n_params > 0) std::fill(grad_out, grad_out + (size_t)B * n_params, 0.0);
+    // row r's derivatives of the gates whose values start at v
+    auto add = [&](const std::vector<int>& gates, const double* v, int r) {
+        const double* prm_row = params + (per_row ? r * params_batch_stride : 0);
+        double* g = grad_out + (size_t)r * n_params;
+        for (int gi : gates) {
+            const TileGate& tg = list.gates[gi];
+            const sv_op& op = ops[tg.op];
+            if (tg.deriv != TD_GENERAL) {
+                g[op.param[0]] += *v++;
+                continue;
+            }
+            double prm[3];
+            op_params(op, info[tg.op], prm_row, prm);
+            cd m[16], md[16], dm[16];
+            kind_matrix(op.kind, prm, m);
+            dagger(1, m, md);
+            for (int d = 0; d < info[tg.op].np; ++d) {
+                kind_dmatrix(op.kind, prm, d, dm);
+                double re = 0.0;
+                for (int a = 0; a < 2; ++a)
+                    for (int b = 0; b < 2; ++b) {
+                        const cd G = dm[a * 2] * md[b] + dm[a * 2 + 1] * md[2 + b];
+                        const double* S = v + 2 * (2 * a + b);
+                        re += G.real() * S[0] - G.imag() * S[1];
+                    }
+                g[op.param[d]] += 2.0 * re;
+            }
+            v += 8;
+        }
+    };
+    if (s->n > kTileMaxBits) {
+        const uint64_t parts = tile_adjoint_parts(B);
+        ensure_scratch(s, parts + std::max<uint64_t>(inner_parts(s->n, B), drift_parts(s->n, B)));
+        double* rscratch = s->scratch + parts;
+        const uint64_t nvals = (uint64_t)nv * B;
+        ensure_dout(s, nvals + 5ull * B);
+        double* d_loss = s->dout + nvals;             // [B][2] re, im
+        double* d_drift = d_loss + 2ull * B;
+        if (diag_w) {
+            launch_diag_lambda(prow, lrow, s->n, diag_w, s->stream);
+        } else {
+            PauliTermDev* dterms = nullptr;
+            const double* dc = nullptr;
+            upload_terms(s, obs, n_obs, coeff_rows, B, &dterms, &dc);
+            launch_apply_pauli_sum(prow, lrow, s->n, dterms, n_obs, dc, s->stream, z_only_terms(obs, n_obs));
+        }
+        launch_inner(prow, lrow, s->n, rscratch, d_loss, s->stream);
+        const Rows both{s->psi, lam, B, 2 * B, s->N};
+        std::vector<TileValues> values;
+        TilePlannerHandle plan(list, s->n, B);
+        TileSweep w;
+        while (plan.next(w)) {
+            bool plain = w.single;
+            for (int gi : w.gates) plain = plain && list.gates[gi].deriv == TD_NONE;
+            if (!plain) {
+                tile_adjoint_sweep(s->psi, lam, s->n, B, list, w, s->scratch, s->dout, values, s->stream);
+                continue;
+            }
+            for (int gi : w.gates) {
+                const sv_op& op = ops[list.gates[gi].op];
+                const OpInfo& oi = info[list.gates[gi].op];
+                cd m[16], md[16];
+                op_matrix(op, oi, params, m);
+                dagger(oi.k, m, md);
+                dispatch(both, oi.k, op.targets, op.n_controls, op.controls, md, s->stream);
+            }
+        }
+        launch_drift(prow, s->n, rscratch, d_drift, s->stream);
+        fetch(s, nvals + 3ull * B);
+        for (const TileValues& t : values)
+            for (int r = 0; r < t.rows; ++r) add(t.gates, s->hout + t.at + (uint64_t)r * t.nvalues, t.row0 + r);
+        for (int r = 0; r < B; ++r) {
+            if (loss_out) loss_out[r] = s->hout[nvals + 2 * r];
+            if (drift_out) drift_out[r] = std::sqrt(std::max(0.0, s->hout[nvals + 2ull * B + r]));
+        }
+        return;
+    }
     const uint64_t per = (uint64_t)nv + 2;
     ensure_dout(s, per * B);
-    const Rows prow{s->psi, s->psi, B, B, s->N}, lrow{lam, lam, B, B, s->N};
     const double* dcoeff = nullptr;
     int coeff_stride = 0;
     if (diag_w) {
@@ -768,36 +846,8 @@ void adjoint_tile(sv_state s, const sv_op* ops, const std::vector<OpInfo>& info,
     std::vector<int> order;
     tile_adjoint(s->psi, lam, s->n, B, list, dcoeff, coeff_stride, s->dout, order, s->stream);
     fetch(s, per * B);
-    if (n_params > 0) std::fill(grad_out, grad_out + (size_t)B * n_params, 0.0);
     for (int r = 0; r < B; ++r) {
-        const double* v = s->hout + per * r;
-        const double* prm_row = params + (per_row ? r * params_batch_stride : 0);
-        double* g = grad_out + (size_t)r * n_params;
-        for (int gi : order) {
-            const TileGate& tg = list.gates[gi];
-            const sv_op& op = ops[tg.op];
-            if (tg.deriv != TD_GENERAL) {
-                g[op.param[0]] += *v++;
-                continue;
-            }
-            double prm[3];
-            op_params(op, info[tg.op], prm_row, prm);
-            cd m[16], md[16], dm[16];
-            kind_matrix(op.kind, prm, m);
-            dagger(1, m, md);
-            for (int d = 0; d < info[tg.op].np; ++d) {
-                kind_dmatrix(op.kind, prm, d, dm);
-                double re = 0.0;
-                for (int a = 0; a < 2; ++a)
-                    for (int b = 0; b < 2; ++b) {
-                        const cd G = dm[a * 2] * md[b] + dm[a * 2 + 1] * md[2 + b];
-                        const double* S = v + 2 * (2 * a + b);
-                        re += G.real() * S[0] - G.imag() * S[1];
-                    }
-                g[op.param[d]] += 2.0 * re;
-            }
-            v += 8;
-        }
+        add(order, s->hout + per * r, r);
         const double* tail = s->hout + per * r + nv;
         if (loss_out) loss_out[r] = tail[0];
         if (drift_out) drift_out[r] = std::sqrt(std::max(0.0, tail[1]));

@@ -455,8 +455,9 @@ public:
     // launch(args, rows, derivative gates in the order of their values, last)
     using Launch = std::function<void(const TileArgs&, int, const std::vector<int>&, bool)>;
 
-    Emitter(const Rows& rows, int n, const TileList& l, uint64_t S, int R, Launch launch)
-        : rows_(rows), l_(l), pl_(n, S), R_(R), launch_(std::move(launch)), min_rows_(std::min(rows.nrows, kMinRows))
+    Emitter(const Rows& rows, int n, const TileList& l, uint64_t S, int R, Launch launch, int max_values = kAdjValues)
+        : rows_(rows), l_(l), pl_(n, S), R_(R), launch_(std::move(launch)), min_rows_(std::min(rows.nrows, kMinRows)),
+          max_values_(max_values)
     {
         std::memset(&a_, 0, sizeof(a_));
         a_.p0 = rows.p0;
@@ -639,7 +640,7 @@ private:
         const int mw = kMatFloats[g.kind];
         const int words = g.per_row ? mw * min_rows_ : mw;
         const int values = value_count(g);
-        if (nvalues_ + values > kAdjValues) return false;
+        if (nvalues_ + values > max_values_) return false;
         if (g.kind <= TK_DIAG1 && g.nc == 0 && in_registers(e.r, g.targets[0])) {
             const int b = e.r.reg_index(pl_.tile_bit[g.targets[0]]);
             int at = e.last[b] + 1;
@@ -815,7 +816,7 @@ private:
     Places pl_;
     int R_;
     Launch launch_;
-    int min_rows_;
+    int min_rows_, max_values_;
     TileArgs a_;
     std::vector<Entry> rounds_;
     std::vector<std::pair<int, int>> order_;
@@ -884,7 +885,7 @@ void tile_sweep(const Rows& rows, int n, const TileList& l, const TileSweep& s, 
     em.flush();
 }
 
-bool tile_adjoint_applies(int n) { return n >= kTileRegBits && n <= kTileMaxBits; }
+bool tile_adjoint_applies(int n) { return n >= kTileRegBits; }
 
 int tile_values(const TileList& l)
 {
@@ -904,6 +905,7 @@ void tile_adjoint(float2* psi, float2* lam, int n, int rows, const TileList& l, 
     a.coeff_stride = coeff_stride;
     a.out = out;
     a.out_stride = tile_values(l) + 2;
+    a.N = 1ull << n;
     a.T = n;
     a.first = 1;
     order.clear();
@@ -917,7 +919,7 @@ void tile_adjoint(float2* psi, float2* lam, int n, int rows, const TileList& l, 
         for (int gi : gates) a.nvalues += value_count(l.gates[gi]);
         a.last = last;
         std::memcpy(a.words, t.words, sizeof(a.words));
-        launch_tile_adj(a, nr, st);
+        launch_tile_adj(a, 1, nr, st);
         if (t.row0 + nr < rows) return;
         order.insert(order.end(), gates.begin(), gates.end());
         a.value0 += a.nvalues;
@@ -928,6 +930,57 @@ void tile_adjoint(float2* psi, float2* lam, int n, int rows, const TileList& l, 
     for (size_t i = 0; i < all.size(); ++i) all[i] = (int)i;
     emit_rounds(em, n, l, all, S, R);
     em.flush(true);
+}
+
+namespace {
+
+// Workgroups per row of a sweep: two per compute unit over all rows (their
+// LDS), each taking several tiles, so that values are summed over few parts.
+int adjoint_grid(uint64_t tiles, int rows)
+{
+    const uint64_t most = 2 * (uint64_t)device_info().cu_count;
+    while (tiles > 1 && tiles * rows > most) tiles /= 2;
+    return (int)tiles;
+}
+
+}  // namespace
+
+uint64_t tile_adjoint_parts(int rows)
+{
+    return (uint64_t)kAdjTileValues * std::max<uint64_t>(2 * (uint64_t)device_info().cu_count, rows);
+}
+
+void tile_adjoint_sweep(float2* psi, float2* lam, int n, int rows, const TileList& l, const TileSweep& s, double* part,
+                        double* out, std::vector<TileValues>& values, hipStream_t st)
+{
+    constexpr int R = kTileRegBits - 1;
+    TileAdjArgs a{};
+    a.psi = psi;
+    a.lam = lam;
+    a.out = part;
+    a.N = 1ull << n;
+    const Rows rr{psi, psi, rows, rows, a.N};
+    Emitter em(
+        rr, n, l, s.qubits, R,
+        [&](const TileArgs& t, int nr, const std::vector<int>& gates, bool) {
+            a.T = t.T;
+            a.row0 = t.row0;
+            a.nrounds = t.nrounds;
+            a.nwords = t.nwords;
+            a.nvalues = 0;
+            for (int gi : gates) a.nvalues += value_count(l.gates[gi]);
+            std::memcpy(a.pos, t.pos, sizeof(a.pos));
+            std::memcpy(a.words, t.words, sizeof(a.words));
+            const int grid = adjoint_grid(a.N >> a.T, nr);
+            launch_tile_adj(a, grid, nr, st);
+            if (a.nvalues == 0) return;
+            const uint64_t at = values.empty() ? 0 : values.back().at + (uint64_t)values.back().rows * values.back().nvalues;
+            launch_sum_slots(part, grid, nr * a.nvalues, out + at, st);
+            values.push_back(TileValues{t.row0, nr, a.nvalues, at, gates});
+        },
+        kAdjTileValues);
+    emit_rounds(em, n, l, s.gates, s.qubits, R);
+    em.flush();
 }
 
 // ------------------------------------------------------------ Pauli strings

@@ -116,14 +116,16 @@ constexpr uint32_t kTileSwz[8] = {3, 5, 9, 6, 10, 12, 7, 11};
 
 void launch_tile(const TileArgs& a, int rows, int reg_bits, hipStream_t st);
 
-// The adjoint of a state of at most kTileMaxBits qubits: rows [row0, row0 +
-// grid), a tile each.
+// The adjoint: of a state of at most kTileMaxBits qubits (a tile per row), or
+// one sweep of a larger one (kTileMaxBits qubits a tile).
 constexpr int kAdjValues = 256;       // derivative values of a launch
+constexpr int kAdjTileValues = 128;   // of a launch over several tiles: two workgroups' LDS in a compute unit
 struct TileAdjArgs {
     float2* psi;
     float2* lam;
     const double* coeff;              // NULL: lambda is loaded; else lambda = sum_q coeff[row][q] Z_q psi
-    double* out;                      // per row: the values, then loss, drift
+    double* out;                      // one tile: per row the values, then loss, drift; several: [rows][nvalues][grid]
+    uint64_t N;
     int64_t out_stride;
     int coeff_stride;
     int row0;
@@ -133,10 +135,11 @@ struct TileAdjArgs {
     int value0;                       // first value of this launch
     int nvalues;
     int first, last;                  // writes the loss, the drift
+    uint8_t pos[kTileMaxBits];        // tile qubits, ascending
     uint32_t words[kTileWords + kTilePad];
 };
 static_assert(sizeof(TileAdjArgs) <= 4096 - 128, "kernel arguments stay within 4 KiB");
-void launch_tile_adj(const TileAdjArgs& a, int rows, hipStream_t st);
+void launch_tile_adj(const TileAdjArgs& a, int grid, int rows, hipStream_t st);
 
 // Pauli strings whose x bits lie in one tile (k_pauli.hip). Words: per
 // distinct x and part [0] x (tile bits) | 1 << 12: the products' imaginary
@@ -233,6 +236,18 @@ bool tile_adjoint_applies(int n);
 int tile_values(const TileList& l);
 void tile_adjoint(float2* psi, float2* lam, int n, int rows, const TileList& l, const double* coeff, int coeff_stride,
                   double* out, std::vector<int>& order, hipStream_t st);
+
+// One sweep of the adjoint of a larger state: part (tile_adjoint_parts
+// doubles) is its workspace. Every launch appends its values, [rows][nvalues]
+// doubles at `out`, to `values`.
+struct TileValues {
+    int row0, rows, nvalues;
+    uint64_t at;                      // first double, from `out`
+    std::vector<int> gates;           // whose values follow each other
+};
+uint64_t tile_adjoint_parts(int rows);
+void tile_adjoint_sweep(float2* psi, float2* lam, int n, int rows, const TileList& l, const TileSweep& s, double* part,
+                        double* out, std::vector<TileValues>& values, hipStream_t st);
 
 template <class F>
 void tile_run(const Rows& rows, int n, const TileList& l, hipStream_t st, const F& one_gate)

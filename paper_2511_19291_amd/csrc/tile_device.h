@@ -395,6 +395,28 @@ __device__ __forceinline__ double plus_lane(double v)
     return v + __longlong_as_double((long long)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo));
 }
 
+// v of another lane (a DPP move without masks)
+template <int CTRL>
+__device__ __forceinline__ double lane_move(double v)
+{
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+
+// v plus v of lane ^ D, D = 16 or 32: the swap exchanges the odd groups of D
+// lanes of one register with the even ones of the other.
+template <int D>
+__device__ __forceinline__ double add_swapped(double v)
+{
+    auto swap = [](int w) SV_INLINE {
+        if constexpr (D == 16) return __builtin_amdgcn_permlane16_swap((uint32_t)w, (uint32_t)w, false, false);
+        else return __builtin_amdgcn_permlane32_swap((uint32_t)w, (uint32_t)w, false, false);
+    };
+    const auto lo = swap(__double2loint(v)), hi = swap(__double2hiint(v));
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+
 // the wave's sum, in lane 63
 __device__ __forceinline__ double wave_sum(double v)
 {

@@ -181,7 +181,8 @@ static void run_tile(const TileArgs& a, int R, uint32_t tile, int y)
 }
 
 namespace sv {
-void launch_tile_adj(const TileAdjArgs&, int, hipStream_t) { std::abort(); }
+void launch_tile_adj(const TileAdjArgs&, int, int, hipStream_t) { std::abort(); }
+void launch_sum_slots(const double*, int, int, double*, hipStream_t) { std::abort(); }
 void launch_tile(const TileArgs& a, int rows, int reg_bits, hipStream_t)
 {
     ++launches;
