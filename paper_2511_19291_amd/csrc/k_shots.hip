@@ -55,6 +55,18 @@ __device__ double wg_sum256(double v, double* sh)
 // 2^kChunkBits (128: one float4 per lane of a wave).
 constexpr int kChunkBits = 7;
 static_assert(kShotBits - kChunkBits <= 6, "a lane per chunk");
+// Many draws: the mass pass also keeps the sums of 2^kSubBits amplitudes (one
+// line), and a draw reads these eight and one line instead of its chunk of 1 KiB.
+// At 27 qubits the pass takes 215 us instead of 190, the reads of 2^20 draws
+// 90 instead of 262: worth it from a draw per 880 amplitudes on. The sums take
+// 1/16 of the state (0.5 GiB at kSubMaxBits qubits, the limit).
+constexpr int kSubBits = 4;
+constexpr int kSubMaxBits = 30;
+
+bool keeps_subs(int n, int64_t shots)
+{
+    return n >= kChunkBits && n <= kSubMaxBits && shots >= ((int64_t)1 << n) / 880;
+}
 
 // 1. probability mass of each block of 2^bb amplitudes (bb <= kShotBits).
 // Blocks of at least 128 amplitudes (k_chunk_mass): one workgroup of eight
@@ -69,7 +81,8 @@ static_assert(kShotBits - kChunkBits <= 6, "a lane per chunk");
 // per block with two passes of sixteen chunks 1.85 ms.)
 constexpr int kMassThreads = 512;
 __global__ __launch_bounds__(kMassThreads) void k_chunk_mass(const float2* __restrict__ psi, int bb,
-                                                            double* __restrict__ mass, double* __restrict__ csum)
+                                                            double* __restrict__ mass, double* __restrict__ csum,
+                                                            double* __restrict__ sub)
 {
     __shared__ double sh[1 << (kShotBits - kChunkBits)];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -83,6 +96,22 @@ __global__ __launch_bounds__(kMassThreads) void k_chunk_mass(const float2* __res
         double t[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) t[i] = prob(make_float2(v[i].x, v[i].y)) + prob(make_float2(v[i].z, v[i].w));
+        if (sub) {
+            // sums of 16 amplitudes (eight lanes) of the four chunks, by the same
+            // kind of butterfly: xor 4, 2 halve, xor 1 finishes
+            const bool b2 = (lane >> 2) & 1, b1 = (lane >> 1) & 1;
+            double v2[2];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const double keep = b2 ? t[2 + j] : t[j], send = b2 ? t[j] : t[2 + j];
+                v2[j] = keep + __shfl_xor(send, 4, 64);
+            }
+            double v1 = (b1 ? v2[1] : v2[0]) + __shfl_xor(b1 ? v2[0] : v2[1], 2, 64);
+            v1 += __shfl_xor(v1, 1, 64);
+            const uint32_t ch = 4 * w + 2 * b2 + b1;
+            if ((lane & 1) == 0 && ch < nch)
+                sub[((uint64_t)blockIdx.x << (kShotBits - kSubBits)) + 8 * ch + (lane >> 3)] = v1;
+        }
         const bool b5 = (lane >> 5) & 1, b4 = (lane >> 4) & 1;
         double u2[2];
 #pragma unroll
@@ -255,9 +284,10 @@ __device__ __forceinline__ double group_incl8(double v, int gi)
     return v;
 }
 
+template <bool SUB>
 __device__ __forceinline__ void resolve_group(const float2* __restrict__ psi, int bb, const uint32_t* __restrict__ order,
                                               const uint32_t* __restrict__ blk, const double* __restrict__ rem,
-                                              const double* __restrict__ csum, uint32_t j, bool valid, int lane,
+                                              const double* __restrict__ csum, const double* __restrict__ sub, uint32_t j, bool valid, int lane,
                                               int64_t* __restrict__ out)
 {
     const int gi = lane & 7;                          // lane within the shot's group
@@ -308,31 +338,36 @@ __device__ __forceinline__ void resolve_group(const float2* __restrict__ psi, in
     // lane gi amplitudes 16 t + 2 gi, 16 t + 2 gi + 1 (pair sum q[t]), so
     // sub-block t (amplitudes 16 t .. 16 t + 15) sits across the group
     const float4* c4 = reinterpret_cast<const float4*>(psi + ((uint64_t)b << bb) + ((uint64_t)chunk << kChunkBits)) + gi;
-    float4 v[8];
+    double p0[8], p1[8], stot;
+    if constexpr (SUB) {
+        stot = valid ? sub[((uint64_t)b << (kShotBits - kSubBits)) + 8 * chunk + gi] : 0.0;
+    } else {
+        float4 v[8];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) v[t] = valid ? c4[8 * t] : make_float4(0.f, 0.f, 0.f, 0.f);
-    double p0[8], p1[8], q[8];
+        for (int t = 0; t < 8; ++t) v[t] = valid ? c4[8 * t] : make_float4(0.f, 0.f, 0.f, 0.f);
+        double q[8];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-        p0[t] = prob(make_float2(v[t].x, v[t].y));
-        p1[t] = prob(make_float2(v[t].z, v[t].w));
-        q[t] = p0[t] + p1[t];
+        for (int t = 0; t < 8; ++t) {
+            p0[t] = prob(make_float2(v[t].x, v[t].y));
+            p1[t] = prob(make_float2(v[t].z, v[t].w));
+            q[t] = p0[t] + p1[t];
+        }
+        // sub-block totals by reduce-scatter over the group (lane gi ends with
+        // sub-block gi's total), then their running sums across the group
+        const bool g2 = (gi >> 2) & 1, g1 = (gi >> 1) & 1, g0 = gi & 1;
+        double r4[4], r2[2];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const double keep = g2 ? q[4 + j] : q[j], send = g2 ? q[j] : q[4 + j];
+            r4[j] = keep + __shfl_xor(send, 4, 8);
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const double keep = g1 ? r4[2 + j] : r4[j], send = g1 ? r4[j] : r4[2 + j];
+            r2[j] = keep + __shfl_xor(send, 2, 8);
+        }
+        stot = (g0 ? r2[1] : r2[0]) + __shfl_xor(g0 ? r2[0] : r2[1], 1, 8);
     }
-    // sub-block totals by reduce-scatter over the group (lane gi ends with
-    // sub-block gi's total), then their running sums across the group
-    const bool g2 = (gi >> 2) & 1, g1 = (gi >> 1) & 1, g0 = gi & 1;
-    double r4[4], r2[2];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const double keep = g2 ? q[4 + j] : q[j], send = g2 ? q[j] : q[4 + j];
-        r4[j] = keep + __shfl_xor(send, 4, 8);
-    }
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const double keep = g1 ? r4[2 + j] : r4[j], send = g1 ? r4[j] : r4[2 + j];
-        r2[j] = keep + __shfl_xor(send, 2, 8);
-    }
-    const double stot = (g0 ? r2[1] : r2[0]) + __shfl_xor(g0 ? r2[0] : r2[1], 1, 8);
     // (lane gi now holds sub-block gi's total)
     const double tot_in_order = stot;
     const double sincl = group_incl8(tot_in_order, gi);
@@ -346,12 +381,18 @@ __device__ __forceinline__ void resolve_group(const float2* __restrict__ psi, in
     const double need2 = shit ? need - sbefore : 1e300;
     // inside sub-block T: lane gi's pair (amplitudes 16 T + 2 gi, + 1)
     double a0 = 0.0, a1 = 0.0;
+    if constexpr (SUB) {
+        const float4 v = valid ? c4[8 * T] : make_float4(0.f, 0.f, 0.f, 0.f);
+        a0 = prob(make_float2(v.x, v.y));
+        a1 = prob(make_float2(v.z, v.w));
+    } else {
 #pragma unroll
-    for (int t = 0; t < 8; ++t)
-        if (t == T) {
-            a0 = p0[t];
-            a1 = p1[t];
-        }
+        for (int t = 0; t < 8; ++t)
+            if (t == T) {
+                a0 = p0[t];
+                a1 = p1[t];
+            }
+    }
     const double pincl = group_incl8(a0 + a1, gi);
     const double pup = __shfl_up(pincl, 1, 8);
     const double ppre = gi > 0 ? pup : 0.0;
@@ -373,12 +414,14 @@ __device__ __forceinline__ void resolve_group(const float2* __restrict__ psi, in
         out[sid] = idx >= 0 ? (int64_t)(((uint64_t)b << bb) + ((uint64_t)chunk << kChunkBits) + (uint32_t)idx) : -1;
 }
 
+template <bool SUB>
 __global__ __launch_bounds__(kST) void k_shot_resolve_chunked(const float2* __restrict__ psi, int bb, uint32_t nb,
                                                               const uint32_t* __restrict__ cinc,
                                                               const uint32_t* __restrict__ order,
                                                               const uint32_t* __restrict__ blk,
                                                               const double* __restrict__ rem,
                                                               const double* __restrict__ csum,
+                                                              const double* __restrict__ sub,
                                                               int64_t* __restrict__ out)
 {
     const int lane = threadIdx.x & 63;
@@ -386,7 +429,7 @@ __global__ __launch_bounds__(kST) void k_shot_resolve_chunked(const float2* __re
     const uint64_t nwaves = (uint64_t)gridDim.x * (kST / 64);
     for (uint64_t w = (uint64_t)blockIdx.x * (kST / 64) + (threadIdx.x >> 6); 8 * w < total; w += nwaves) {
         const uint64_t j = 8 * w + (lane >> 3);
-        resolve_group(psi, bb, order, blk, rem, csum, (uint32_t)j, j < total, lane, out);
+        resolve_group<SUB>(psi, bb, order, blk, rem, csum, sub, (uint32_t)j, j < total, lane, out);
     }
 }
 
@@ -916,7 +959,9 @@ size_t shot_scratch_bytes(int n, int64_t shots)
     const uint64_t nb = 1ull << (n - shot_block_bits(n));
     const uint64_t st = scan_tmp(nb);
     const uint64_t nch = (uint64_t)nb << (kShotBits - kChunkBits);   // chunk slots
+    const uint64_t nsub = keeps_subs(n, shots) ? nb << (kShotBits - kSubBits) : 0;
     return (nb + st) * sizeof(double)                 // scanned masses + scan totals
+           + nsub * sizeof(double)                    // sums of 16
            + (3 * nb + st) * sizeof(uint32_t)         // counts, fill, (count scan totals)
            + nch * sizeof(double)                     // chunk masses
            + (uint64_t)shots * (sizeof(double) + 2 * sizeof(uint32_t)) + 80;
@@ -944,9 +989,12 @@ void launch_sample_exact(const ShotLaunch& a, hipStream_t st)
     uint32_t* order = reinterpret_cast<uint32_t*>(take((size_t)a.shots * sizeof(uint32_t)));
     const uint64_t nch = nb << (kShotBits - kChunkBits);
     double* csum = reinterpret_cast<double*>(take(nch * sizeof(double)));
+    double* sub = keeps_subs(a.n, a.shots)
+                      ? reinterpret_cast<double*>(take((nb << (kShotBits - kSubBits)) * sizeof(double)))
+                      : nullptr;
 
     if (bb >= kChunkBits)
-        hipLaunchKernelGGL(k_chunk_mass, dim3((unsigned)nb), dim3(kMassThreads), 0, st, a.psi, bb, mass, csum);
+        hipLaunchKernelGGL(k_chunk_mass, dim3((unsigned)nb), dim3(kMassThreads), 0, st, a.psi, bb, mass, csum, sub);
     else
         hipLaunchKernelGGL(k_block_mass, dim3((unsigned)nb), dim3(kST), 0, st, a.psi, bb, (uint64_t)nb, mass, csum);
     SV_HIP(hipGetLastError());
@@ -969,8 +1017,8 @@ void launch_sample_exact(const ShotLaunch& a, hipStream_t st)
         const uint64_t groups = ((uint64_t)a.shots + 7) / 8;                // waves needed at most
         const unsigned cg = (unsigned)std::max<uint64_t>(
             1, std::min<uint64_t>((groups + 3) / 4, (uint64_t)device_info().cu_count * 16));
-        hipLaunchKernelGGL(k_shot_resolve_chunked, dim3(cg), dim3(kST), 0, st, a.psi, bb, (uint32_t)nb, cinc, order,
-                           blk, rem, csum, a.out);
+        hipLaunchKernelGGL(sub ? k_shot_resolve_chunked<true> : k_shot_resolve_chunked<false>, dim3(cg), dim3(kST), 0, st,
+                           a.psi, bb, (uint32_t)nb, cinc, order, blk, rem, csum, sub, a.out);
     } else {
         hipLaunchKernelGGL(k_shot_resolve, dim3(rg), dim3(kST), 0, st, a.psi, bb, (uint32_t)nb, cinc, cnt, order,
                            rem, csum, a.out);
