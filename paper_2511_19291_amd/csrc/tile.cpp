@@ -229,6 +229,33 @@ int tile_bits(int n) { return std::min(n, kTileMaxBits); }
 
 bool tile_applies(int n) { return n >= kTileRegBits; }
 
+namespace {
+
+// A matrix rounded to FP32 scales every state by 1 + some 1e-8, a list of
+// gates by the sum of these: 1e-6 after hundreds of rotations, four times that
+// in the derivatives of a backward. So each matrix that is not exact is scaled
+// first by what the gates before it left over (`drift`, a logarithm of the norm),
+// which keeps the sum within one rounding.
+void keep_norm(cd* m, int count, double& drift)
+{
+    double want = 0.0, got = 0.0;
+    bool exact = true;
+    const double f = 1.0 - drift;
+    for (int i = 0; i < count; ++i) {
+        exact = exact && (double)(float)m[i].real() == m[i].real() && (double)(float)m[i].imag() == m[i].imag();
+        want += std::norm(m[i]);
+        const double re = (float)(f * m[i].real()), im = (float)(f * m[i].imag());
+        got += re * re + im * im;
+    }
+    if (exact) return;
+    const double left = drift + 0.5 * std::log(got / want);          // `got` holds the factor f
+    if (!(std::abs(left) < 1e-6)) return;              // not finite, or not a rounding
+    for (int i = 0; i < count; ++i) m[i] *= f;
+    drift = left;
+}
+
+}  // namespace
+
 void tile_append(TileList& l, int k, const int* targets, int nc, const int* controls, const cd* ms, int nm, int op,
                  int deriv)
 {
@@ -277,8 +304,12 @@ void tile_append(TileList& l, int k, const int* targets, int nc, const int* cont
         g.kind = nc > 0 ? TK_DENSE : real ? TK_REAL : imoff ? TK_IMOFF : TK_DENSE;
     }
     if (kMatFloats[g.kind] == 0) g.per_row = false;
+    if (g.per_row) l.row_drift.resize(std::max<size_t>(l.row_drift.size(), nm), 0.0);
     for (int r = 0; r < (g.per_row ? nm : 1); ++r) {
-        const cd* m = ms + (size_t)r * D * D;
+        cd m[16];
+        std::copy(ms + (size_t)r * D * D, ms + (size_t)(r + 1) * D * D, m);
+        // uncontrolled: every amplitude takes part
+        if (nc == 0 && g.k > 0) keep_norm(m, D * D, g.per_row ? l.row_drift[r] : l.drift);
         auto put = [&](cd v) {
             l.pool.push_back((float)v.real());
             l.pool.push_back((float)v.imag());

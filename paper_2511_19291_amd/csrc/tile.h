@@ -196,6 +196,8 @@ struct TileGate {
 struct TileList {
     std::vector<TileGate> gates;
     std::vector<float> pool;
+    double drift = 0.0;               // of the norm by the matrices' rounding (logarithm)
+    std::vector<double> row_drift;    // by each row's own matrices
 };
 
 // Append (matrices, targets, controls): `ms` holds nm matrices of 4^k entries

@@ -31,3 +31,11 @@ def program(tmp_path_factory):
 def test_programs_equal_the_gates(program, units):
     r = subprocess.run([program, "0", "200", str(units)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_roundings_do_not_add_up_in_the_norm(program):
+    """3000 matrices, rounded to FP32 one after the other, scale a state by no
+    more than one rounding (2^-24) in all: one angle that by itself would
+    drift, random rotations, general gates, phases, matrices per row."""
+    r = subprocess.run([program, "norms"], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout + r.stderr

@@ -233,8 +233,59 @@ static void apply(const Gate& g, int rows, uint64_t N, std::vector<cd>& v)
         }
 }
 
+// The scale of a list's matrices as the kernels get them, and as each would be
+// rounded by itself: logarithms, summed over the uncontrolled gates; per row.
+static int norms()
+{
+    const double kRounding = std::ldexp(1.01, -24);
+    std::mt19937 rng(1);
+    std::uniform_real_distribution<double> u(-1.0, 1.0);
+    double angle = 0.0, most = 0.0;               // the angle whose rounded rotation scales most
+    for (int i = 1; i <= 400; ++i) {
+        const double a = 0.0005 * i, c = (float)std::cos(a), s = (float)std::sin(a), e = std::abs(c * c + s * s - 1.0) / 2;
+        if (e > most) {
+            most = e;
+            angle = a;
+        }
+    }
+    for (int mode = 0; mode < 5; ++mode) {
+        const int rows = mode == 4 ? 3 : 1;
+        sv::TileList list;
+        double alone = 0.0;
+        for (int i = 0; i < 3000; ++i) {
+            std::vector<cd> ms;
+            for (int r = 0; r < rows; ++r) {
+                const double a = mode < 2 ? angle : 3.0 * u(rng), c = std::cos(a), s = std::sin(a);
+                const cd p = std::polar(1.0, 3.0 * u(rng)), q = std::polar(1.0, 3.0 * u(rng));
+                if (mode == 0 || mode == 4) ms.insert(ms.end(), {c, cd(0, -s), cd(0, -s), c});
+                else if (mode == 1) ms.insert(ms.end(), {c, -s, s, c});
+                else if (mode == 2) ms.insert(ms.end(), {c, -s * p, s * q, c * p * q});
+                else ms.insert(ms.end(), {std::conj(p), 0.0, 0.0, p});
+            }
+            if (mode == 0) alone += 0.5 * std::log(std::pow((double)(float)std::cos(angle), 2) + std::pow((double)(float)std::sin(angle), 2));
+            const int t = i % 6;
+            sv::tile_append(list, 1, &t, 0, nullptr, ms.data(), rows, i);
+        }
+        if (mode == 0 && std::abs(alone) < 1000 * kRounding * 0.3) return 1;      // the list would drift
+        for (int r = 0; r < rows; ++r) {
+            double sum = 0.0;
+            for (const sv::TileGate& g : list.gates) {
+                const int words = g.kind == sv::TK_DENSE ? 8 : 4;
+                const float* w = list.pool.data() + g.mat + (g.per_row ? r * words : 0);
+                double s = 0.0;
+                for (int i = 0; i < words; ++i) s += (double)w[i] * w[i];
+                sum += 0.5 * std::log(s / 2);
+            }
+            std::printf("mode %d row %d: %.3g\n", mode, r, sum);
+            if (list.gates.size() != 3000 || std::abs(sum) > kRounding) return 1;
+        }
+    }
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
+    if (argc == 2) return norms();
     if (argc != 4) return 2;
     const int first = std::atoi(argv[1]), count = std::atoi(argv[2]);
     cu_count = std::atoi(argv[3]);
