@@ -18,8 +18,10 @@
 // 400, bound by memory), which two workgroups per CU keep 72 % busy; BF16x3 by
 // memory. The planned 20-layer brickwork: FP32 at 27 qubits 45 blocks in 19 sweeps,
 // 18.0 -> 15.1 ms; BF16x3 at 26 qubits 45 blocks in 26 sweeps, 8.5 -> 5.5 ms.
-// Both parts' operands read at once, and priorities that let one workgroup
-// run ahead, changed nothing.
+// What the pause between the products is was not found: both parts' operands read
+// at once, priorities or a delay that let one workgroup run ahead, tiles of 2^12
+// with three workgroups per CU (335 us a block as now), and a persistent grid with
+// the next tile's loads in flight (869 us a sweep instead of 820) gained nothing.
 #include "sv_device.h"
 #include "sv_internal.h"
 #include "tile_device.h"
