@@ -133,14 +133,16 @@ __global__ __launch_bounds__(256) void k_pauli_tile(PauliTileArgs a)
 
 }  // namespace
 
-int pauli_tile_grid(int n, int T)
+// Workgroups per row: four per compute unit over all rows.
+int pauli_tile_grid(int n, int T, int rows)
 {
-    return (int)std::min<uint64_t>(1ull << (n - T), (uint64_t)device_info().cu_count * 4);
+    const uint64_t most = std::max<uint64_t>(1, (uint64_t)device_info().cu_count * 4 / rows);
+    return (int)std::min<uint64_t>(1ull << (n - T), most);
 }
 
 void launch_pauli_tile(const PauliTileArgs& a, int rows, double* out, hipStream_t st)
 {
-    const int n = __builtin_ctzll(a.N), grid = pauli_tile_grid(n, a.T);
+    const int n = __builtin_ctzll(a.N), grid = pauli_tile_grid(n, a.T, rows);
     hipLaunchKernelGGL(k_pauli_tile, dim3((unsigned)grid, (unsigned)rows), dim3((unsigned)std::max(64, 1 << (a.T - 4))), 0,
                        st, a);
     SV_HIP(hipGetLastError());

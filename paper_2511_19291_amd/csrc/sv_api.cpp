@@ -674,7 +674,7 @@ sv_status sv_expval_pauli(sv_state s, const sv_pauli_term* terms, int n_terms, d
         }
         uint64_t parts = groups.empty() ? 0 : pauli_parts(s->n, s->batch, 8);
         for (const PauliSweep& w : sweeps)
-            parts = std::max(parts, (uint64_t)s->batch * w.args.nterms * pauli_tile_grid(s->n, w.args.T));
+            parts = std::max(parts, (uint64_t)s->batch * w.args.nterms * pauli_tile_grid(s->n, w.args.T, s->batch));
         ensure_scratch(s, parts);
         ensure_dout(s, (uint64_t)s->batch * n_terms);
         uint64_t off = 0;

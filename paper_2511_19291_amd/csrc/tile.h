@@ -161,7 +161,7 @@ struct PauliTileArgs {
     uint32_t words[3 * kPauliTerms];
 };
 static_assert(sizeof(PauliTileArgs) <= 4096 - 128, "kernel arguments stay within 4 KiB");
-int pauli_tile_grid(int n, int T);
+int pauli_tile_grid(int n, int T, int rows);
 // out: [rows][nterms]
 void launch_pauli_tile(const PauliTileArgs& a, int rows, double* out, hipStream_t st);
 
