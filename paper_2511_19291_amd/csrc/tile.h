@@ -13,6 +13,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
 #include <cstdint>
 #include <vector>
 
@@ -102,9 +103,10 @@ struct TileArgs {
     int nrounds;
     int nwords;                       // words in use
     uint8_t pos[kTileMaxBits];        // tile qubits, ascending
-    uint32_t words[kTileWords + kTilePad];
+    alignas(16) uint32_t words[kTileWords + kTilePad];   // read 16 bytes at a time
 };
 static_assert(sizeof(TileArgs) <= 4096 - 128, "kernel arguments stay within 4 KiB");
+static_assert(offsetof(TileArgs, words) % 16 == 0, "a program starts at a 16-byte word");
 
 // Swizzle of a tile index into its LDS element: tile bit b >= 4 also flips
 // the low four bits by kTileSwz[b - 4]. The columns of the twelve bits in the
@@ -136,9 +138,10 @@ struct TileAdjArgs {
     int nvalues;
     int first, last;                  // writes the loss, the drift
     uint8_t pos[kTileMaxBits];        // tile qubits, ascending
-    uint32_t words[kTileWords + kTilePad];
+    alignas(16) uint32_t words[kTileWords + kTilePad];   // read 16 bytes at a time
 };
 static_assert(sizeof(TileAdjArgs) <= 4096 - 128, "kernel arguments stay within 4 KiB");
+static_assert(offsetof(TileAdjArgs, words) % 16 == 0, "a program starts at a 16-byte word");
 void launch_tile_adj(const TileAdjArgs& a, int grid, int rows, hipStream_t st);
 
 // Pauli strings whose x bits lie in one tile (k_pauli.hip). Words: per
