@@ -932,7 +932,8 @@ int batch_max_wg_per_cu(int threads, int tile_bits, int phase_mode)
     int nb = 0;
     const size_t lds = batch_lds_bytes(tile_bits);
     void* f = batch_kernel_for(threads, phase_mode);
-    SV_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    // the limit is the function's: the widest tile's, which no other plan lowers
+    SV_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)batch_lds_bytes(kMaxTileBits)));
     SV_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, threads, lds));
     return std::max(nb, 1);
 }

@@ -393,11 +393,18 @@ __global__ __launch_bounds__(1 << kTBits, TILES ? 4 : 2) void k_tile_adj(TileAdj
 void launch_tile_adj(const TileAdjArgs& a, int grid, int rows, hipStream_t st)
 {
     const int threads = std::max(64, 1 << (a.T - kR));
-    const size_t lds = ((size_t)2 << a.T) * sizeof(float2) + (size_t)(a.nvalues + 2) * (threads / 64) * sizeof(double);
+    auto lds_bytes = [](int T, int values, int waves) {
+        return ((size_t)2 << T) * sizeof(float2) + (size_t)(values + 2) * waves * sizeof(double);
+    };
+    const size_t lds = lds_bytes(a.T, a.nvalues, threads / 64);
     const bool tiles = (a.N >> a.T) > 1;
     const void* f = tiles ? reinterpret_cast<const void*>(&k_tile_adj<true>) : reinterpret_cast<const void*>(&k_tile_adj<false>);
-    // two tiles of 2^12 and the values are more than the 64 KiB a launch has by default
-    if (lds > 65536) SV_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    // Two tiles of 2^12 and the values are more than the 64 KiB a launch has by
+    // default. The limit is the function's, not the launch's: always the largest
+    // launch's, so that no thread lowers it between another's call and launch.
+    if (lds > 65536)
+        SV_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   (int)lds_bytes(kTileMaxBits, tiles ? kAdjTileValues : kAdjValues, 1 << (kTBits - 6))));
     if (tiles)
         hipLaunchKernelGGL(k_tile_adj<true>, dim3((unsigned)grid, (unsigned)rows), dim3((unsigned)threads), lds, st, a);
     else
