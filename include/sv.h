@@ -159,8 +159,12 @@ typedef struct sv_op {
  * qubits on, a sweep of the state takes as many of the gates as fit its
  * tiles (2^12 amplitudes held in LDS; controls and phases may be on any
  * qubit): gates that commute may change places, each is still applied on its
- * own in FP32. A gate that no other can share a sweep with runs as in
- * sv_apply_gate. Queues kernels only (no upload, no allocation on the
+ * own in FP32. A matrix without controls is scaled, before it is rounded to
+ * FP32, by what the rounding of those before it in the list took from the
+ * norm or added to it (some 1e-8), so a gate's last bit depends on its place;
+ * the first gate, and a list of one, are as in sv_apply_gate. A gate that no
+ * other can share a sweep with takes a sweep of its own with that same
+ * matrix. Queues kernels only (no upload, no allocation on the
  * device), so it can be captured.
  *   params: host doubles; row r of the batch reads
  *     params[r * params_batch_stride + op.param[j]] (stride 0 = shared).

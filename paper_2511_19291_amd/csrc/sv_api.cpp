@@ -598,7 +598,14 @@ sv_status sv_run(sv_state s, const sv_op* ops, int n_ops, const double* params, 
             for (int r = 0; r < nm; ++r) op_matrix(ops[i], info[i], params + r * params_batch_stride, &ms[(size_t)r * DD]);
             tile_append(list, info[i].k, ops[i].targets, ops[i].n_controls, ops[i].controls, ms.data(), nm, i);
         }
-        tile_run(all_rows(s), s->n, list, s->stream, one_gate);
+        // a gate in a sweep of its own: the same matrix as in a program
+        tile_run(all_rows(s), s->n, list, s->stream, [&](const TileGate& g) {
+            cd m[16];
+            for (int r = 0; r < (g.per_row ? s->batch : 1); ++r) {
+                tile_matrix(list, g, r, m);
+                dispatch(g.per_row ? one_row(s, s->psi, r) : all_rows(s), g.k, g.targets, g.nc, g.controls, m, s->stream);
+            }
+        });
     });
 }
 
@@ -797,13 +804,11 @@ void adjoint_tile(sv_state s, const sv_op* ops, const std::vector<OpInfo>& info,
                 tile_adjoint_sweep(s->psi, lam, s->n, B, list, w, s->scratch, s->dout, values, s->stream);
                 continue;
             }
-            for (int gi : w.gates) {
-                const sv_op& op = ops[list.gates[gi].op];
-                const OpInfo& oi = info[list.gates[gi].op];
-                cd m[16], md[16];
-                op_matrix(op, oi, params, m);
-                dagger(oi.k, m, md);
-                dispatch(both, oi.k, op.targets, op.n_controls, op.controls, md, s->stream);
+            for (int gi : w.gates) {                  // without a parameter: one matrix for all rows
+                const TileGate& g = list.gates[gi];
+                cd m[16];
+                tile_matrix(list, g, 0, m);
+                dispatch(both, g.k, g.targets, g.nc, g.controls, m, s->stream);
             }
         }
         launch_drift(prow, s->n, rscratch, d_drift, s->stream);

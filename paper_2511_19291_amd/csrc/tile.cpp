@@ -235,7 +235,9 @@ namespace {
 // gates by the sum of these: 1e-6 after hundreds of rotations, four times that
 // in the derivatives of a backward. So each matrix that is not exact is scaled
 // first by what the gates before it left over (`drift`, a logarithm of the norm),
-// which keeps the sum within one rounding.
+// which keeps the sum within one rounding. Only matrices that every amplitude
+// takes part in (no controls) are counted and scaled; a gate that runs in a
+// sweep of its own takes its scaled matrix along (tile_matrix).
 void keep_norm(cd* m, int count, double& drift)
 {
     double want = 0.0, got = 0.0;
@@ -335,6 +337,34 @@ void tile_append(TileList& l, int k, const int* targets, int nc, const int* cont
         }
     }
     l.gates.push_back(g);
+}
+
+void tile_matrix(const TileList& l, const TileGate& g, int r, cd* m)
+{
+    const int D = 1 << g.k;
+    const float* w = l.pool.data() + g.mat + (g.per_row ? (size_t)r * kMatFloats[g.kind] : 0);
+    std::fill(m, m + D * D, cd(0.0));
+    switch (g.kind) {
+    case TK_DENSE: case TK_DENSE2:
+        for (int i = 0; i < D * D; ++i) m[i] = cd(w[2 * i], w[2 * i + 1]);
+        break;
+    case TK_REAL:
+        for (int i = 0; i < 4; ++i) m[i] = w[i];
+        break;
+    case TK_IMOFF:
+        for (int i = 0; i < 4; ++i) m[i] = i == 0 || i == 3 ? cd(w[i]) : cd(0.0, w[i]);
+        break;
+    case TK_DIAG1: case TK_DIAG2:
+        for (int i = 0; i < D; ++i) m[i * D + i] = cd(w[2 * i], w[2 * i + 1]);
+        break;
+    case TK_ONES: m[0] = cd(w[0], w[1]); break;
+    case TK_SIGN: m[0] = -1.0; break;
+    case TK_MAP:                      // X, or SWAP
+        if (g.k == 1) m[1] = m[2] = 1.0;
+        else m[0] = m[6] = m[9] = m[15] = 1.0;
+        break;
+    default: break;
+    }
 }
 
 // ------------------------------------------------------------ sweeps

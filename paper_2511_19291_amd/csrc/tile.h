@@ -15,6 +15,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <type_traits>
 #include <vector>
 
 #include "sv_internal.h"
@@ -209,8 +210,12 @@ struct TileList {
 void tile_append(TileList& l, int k, const int* targets, int nc, const int* controls, const cd* ms, int nm, int op,
                  int deriv = TD_NONE);
 
+// Row r's matrix of a gate as its program holds it (scaled and rounded): 2^k x
+// 2^k entries by the gate's targets (one entry without any).
+void tile_matrix(const TileList& l, const TileGate& g, int r, cd* m);
+
 // Apply the list to every row, asynchronously on `st`. Gates that a sweep of
-// their own serves better are handed to one_gate(op).
+// their own serves better are handed to one_gate(gate), or one_gate(op).
 template <class F>
 void tile_run(const Rows& rows, int n, const TileList& l, hipStream_t st, const F& one_gate);
 
@@ -261,7 +266,10 @@ void tile_run(const Rows& rows, int n, const TileList& l, hipStream_t st, const 
     TileSweep s;
     while (plan.next(s)) {
         if (s.single)
-            for (int g : s.gates) one_gate(l.gates[g].op);
+            for (int g : s.gates) {
+                if constexpr (std::is_invocable_v<F, const TileGate&>) one_gate(l.gates[g]);
+                else one_gate(l.gates[g].op);
+            }
         else
             tile_sweep(rows, n, l, s, st);
     }

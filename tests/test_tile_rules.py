@@ -32,3 +32,7 @@ def rules(tmp_path_factory):
 
 def test_programs_are_aligned(rules):
     rules("layout")
+
+
+def test_lone_gates_keep_the_lists_matrices(rules):
+    rules("single")

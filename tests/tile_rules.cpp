@@ -1,10 +1,13 @@
 // Rules of the several-gates-per-sweep path (tile.h) that hold without a GPU.
 //
 //   tile_rules layout     the programs lie at multiples of 16 bytes
+//   tile_rules single     gates in sweeps of their own get the list's matrices
+#include <cmath>
 #include <cstddef>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <vector>
 
 #include "../paper_2511_19291_amd/csrc/tile.h"
 
@@ -35,9 +38,79 @@ static int layout()
     return run % 16 == 0 && adj % 16 == 0 && alignof(sv::TileArgs) % 16 == 0 && alignof(sv::TileAdjArgs) % 16 == 0 ? 0 : 1;
 }
 
+// Gates that share no sweep get the matrix that the list keeps for them: it is
+// scaled by what the gates before it left over, and the gates behind it count on
+// that. Every kind of matrix comes back as it was appended, but for that scale
+// and the rounding; and over a list with many lone gates the norm stays within
+// one rounding.
+static int single()
+{
+    using sv::cd;
+    const double c = std::cos(0.3), s = std::sin(0.3);
+    // kinds: general, real, imaginary off-diagonal, phases, exchange, 4 x 4; one matrix or two
+    for (int kind = 0; kind < 9; ++kind)
+        for (int rows = 1; rows <= 2; ++rows) {
+            const int k = kind >= 6 ? 2 : 1, D = 1 << k, targets[2] = {7, 3}, control = 9, nc = kind == 4;
+            std::vector<cd> ms;
+            for (int r = 0; r < rows; ++r) {
+                const double a = 0.4 + r, ca = std::cos(a), sa = std::sin(a);
+                const cd p = std::polar(1.0, 0.3 + r);
+                std::vector<cd> m(D * D);
+                if (kind == 0) m = {ca, -sa * p, sa, ca * p};
+                if (kind == 1) m = {ca, -sa, sa, ca};
+                if (kind == 2) m = {ca, cd(0, -sa), cd(0, -sa), ca};
+                if (kind == 3) m = {std::conj(p), 0.0, 0.0, p};
+                if (kind == 4) m = {1.0, 0.0, 0.0, p};
+                if (kind == 5) m = {0.0, 1.0, 1.0, 0.0};
+                if (kind == 6) for (int i = 0; i < 4; ++i) m[5 * i] = std::polar(1.0, 0.2 * i * i + r);
+                if (kind == 7) m[0] = m[6] = m[9] = m[15] = 1.0;
+                if (kind == 8) m = {ca, 0, 0, -sa * p, 0, ca, -sa, 0, 0, sa, ca, 0, sa, 0, 0, ca * p};
+                ms.insert(ms.end(), m.begin(), m.end());
+            }
+            sv::TileList list;
+            sv::tile_append(list, k, targets, nc, &control, ms.data(), rows, 0);
+            const sv::TileGate& g = list.gates[0];
+            for (int r = 0; r < (g.per_row ? rows : 1); ++r) {
+                cd m[16];
+                sv::tile_matrix(list, g, r, m);
+                if (g.k == 0) {                       // a phase on the all-ones pattern
+                    if (std::abs(m[0] - ms[r * D * D + D * D - 1]) > 2e-7) return 1;
+                    continue;
+                }
+                for (int i = 0; i < D * D; ++i)
+                    if (std::abs(m[i] - ms[r * D * D + i]) > 2e-7) return 1;
+            }
+        }
+    // rotations on twelve qubits, and one on a thirteenth, which is left alone
+    int differ = 0;
+    for (int count = 24; count <= 200; ++count) {
+        sv::TileList list;
+        const int n = 13, last = 12;
+        const cd rx[4] = {c, cd(0, -s), cd(0, -s), c};
+        for (int i = 0; i < count; ++i) {
+            const int q = i % 12;
+            sv::tile_append(list, 1, &q, 0, nullptr, rx, 1, i);
+        }
+        sv::tile_append(list, 1, &last, 0, nullptr, rx, 1, count);
+        const float* want = list.pool.data() + list.gates[count].mat;
+        int lone = 0;
+        bool same = true;
+        sv::tile_run(sv::Rows{nullptr, nullptr, 1, 1, 1ull << n}, n, list, nullptr, [&](const sv::TileGate& g) {
+            cd m[16];
+            sv::tile_matrix(list, g, 0, m);
+            ++lone;
+            same = same && g.op == count && (float)m[0].real() == want[0] && (float)m[1].imag() == want[1];
+            differ += want[0] != (float)c || want[1] != (float)-s;
+        });
+        if (lone != 1 || !same) return 1;
+    }
+    return differ > 0 ? 0 : 1;                        // (the scale is seen at all)
+}
+
 int main(int argc, char** argv)
 {
     if (argc != 2) return 2;
     if (!std::strcmp(argv[1], "layout")) return layout();
+    if (!std::strcmp(argv[1], "single")) return single();
     return 2;
 }
