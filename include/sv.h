@@ -162,10 +162,10 @@ typedef struct sv_op {
  * own in FP32. A matrix without controls is scaled, before it is rounded to
  * FP32, by what the rounding of those before it in the list took from the
  * norm or added to it (some 1e-8), so a gate's last bit depends on its place;
- * the first gate, and a list of one, are as in sv_apply_gate. A gate that no
- * other can share a sweep with takes a sweep of its own with that same
- * matrix. Queues kernels only (no upload, no allocation on the
- * device), so it can be captured.
+ * the first gate, and a list of one, are as in sv_apply_gate. Gates that
+ * share no sweep with others, and a few that each change a small part of the
+ * state, take sweeps of their own with that same matrix. Queues kernels only
+ * (no upload, no allocation on the device), so it can be captured.
  *   params: host doubles; row r of the batch reads
  *     params[r * params_batch_stride + op.param[j]] (stride 0 = shared).
  *   n_params: length of one row of params (indices are checked against it).

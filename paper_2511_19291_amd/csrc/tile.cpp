@@ -369,6 +369,33 @@ void tile_matrix(const TileList& l, const TileGate& g, int r, cd* m)
 
 // ------------------------------------------------------------ sweeps
 
+// In us of this card, both sides measured as lists of two and three gates. A
+// launch of its own takes 2.7 and its part of the state at 7.0 TB/s, no less than
+// 3.3 (a U3 on 20 / 23 / 26 qubits: 6.4, 23, 160); a tile sweep 4 and every
+// amplitude at 5.5 TB/s (20 / 23 / 26 qubits: 7, 28, 199), and no less than 6.5,
+// from 2^16 amplitudes on 7.5: two gates on 18 qubits take 18.0 by themselves,
+// 19.2 in one sweep when waited for (8.0 : 7.3 among others of their kind), on 10
+// qubits 16.7 : 17.0 (7.5 : 6.9), on 16 17.4 : 18.9. Gates of several controls cost a program more
+// (two X with three: 17.0 : 18.3 on 10 qubits, 18.5 : 29.4 on 22). Two CX on 26
+// qubits: 167 : 202, on 22 behind a reset 39 : 44, on 21 10.3 : 9.1. Three gates:
+// 19.1 : 17.3, 10.4 : 7.3 on 10 qubits.
+bool tile_apart(const TileList& l, const int* gates, int count, int n, int rows)
+{
+    constexpr int kFullLine = 4;
+    const double moved = 16.0 * (double)((uint64_t)rows << n);
+    double own = 0.0, tile = std::max(moved < (1 << 20) ? 6.5 : 7.5, 4.0 + moved / 5.5e6);
+    for (int i = 0; i < count; ++i) {
+        const TileGate& g = l.gates[gates ? gates[i] : i];
+        double part = 1.0;
+        for (int j = 0; j < g.nc; ++j)
+            if (g.controls[j] >= kFullLine) part *= 0.5;       // lower ones leave every line touched
+        const int launches = g.per_row ? rows : 1;
+        own += std::max(3.3 * launches, 2.7 * launches + part * moved / 7.0e6);
+        if (g.nc + g.k > 2) tile += 0.5;
+    }
+    return own < tile;
+}
+
 struct TilePlanner {
     const TileList& l;
     int n, rows;
@@ -401,25 +428,14 @@ struct TilePlanner {
         return true;
     }
 
-    // A sweep of the tile kernel moves every amplitude once. One gate, or a
-    // few gates that each touch a small part of a state far beyond the
-    // caches, move less by sweeps of their own; below that size a launch
-    // costs more than the traffic it saves.
+    // Whether the gates of a sweep go faster by sweeps of their own: one gate
+    // always, a few that each touch a small part of the state often.
     bool separate(const TileSweep& s) const
     {
         if (s.gates.size() == 1) return true;
-        if (((uint64_t)rows << n) * 8 < (64ull << 20) || s.gates.size() > 16) return false;
-        double part = 0.0;
-        for (int gi : s.gates) {
-            const TileGate& g = l.gates[gi];
-            double f = 1.0;
-            for (int j = 0; j < g.nc; ++j)
-                if (g.controls[j] >= kFullLine) f *= 0.5;      // lower ones leave every line touched
-            part += f;
-        }
-        return part < 1.0;
+        if (s.gates.size() > 16) return false;
+        return tile_apart(l, s.gates.data(), (int)s.gates.size(), n, rows);
     }
-    static constexpr int kFullLine = 4;
 };
 
 TilePlannerHandle::TilePlannerHandle(const TileList& l, int n, int rows) : p(new TilePlanner(l, n, rows)) {}

@@ -210,6 +210,10 @@ struct TileList {
 void tile_append(TileList& l, int k, const int* targets, int nc, const int* controls, const cd* ms, int nm, int op,
                  int deriv = TD_NONE);
 
+// Whether `count` gates of the list (gates[0..], NULL: the first ones) go faster
+// by sweeps of their own than in one sweep of tiles.
+bool tile_apart(const TileList& l, const int* gates, int count, int n, int rows);
+
 // Row r's matrix of a gate as its program holds it (scaled and rounded): 2^k x
 // 2^k entries by the gate's targets (one entry without any).
 void tile_matrix(const TileList& l, const TileGate& g, int r, cd* m);
@@ -262,14 +266,20 @@ void tile_adjoint_sweep(float2* psi, float2* lam, int n, int rows, const TileLis
 template <class F>
 void tile_run(const Rows& rows, int n, const TileList& l, hipStream_t st, const F& one_gate)
 {
+    auto one = [&](const TileGate& g) {
+        if constexpr (std::is_invocable_v<F, const TileGate&>) one_gate(g);
+        else one_gate(g.op);
+    };
+    // a few gates: what the planner would find, without its 0.5 us
+    if (l.gates.size() <= 3 && tile_apart(l, nullptr, (int)l.gates.size(), n, rows.nrows)) {
+        for (const TileGate& g : l.gates) one(g);
+        return;
+    }
     TilePlannerHandle plan(l, n, rows.nrows);
     TileSweep s;
     while (plan.next(s)) {
         if (s.single)
-            for (int g : s.gates) {
-                if constexpr (std::is_invocable_v<F, const TileGate&>) one_gate(l.gates[g]);
-                else one_gate(l.gates[g].op);
-            }
+            for (int g : s.gates) one(l.gates[g]);
         else
             tile_sweep(rows, n, l, s, st);
     }

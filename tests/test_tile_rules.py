@@ -36,3 +36,7 @@ def test_programs_are_aligned(rules):
 
 def test_lone_gates_keep_the_lists_matrices(rules):
     rules("single")
+
+
+def test_short_lists_take_the_faster_sweeps(rules):
+    rules("short")

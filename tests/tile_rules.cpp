@@ -1,6 +1,7 @@
 // Rules of the several-gates-per-sweep path (tile.h) that hold without a GPU.
 //
 //   tile_rules layout     the programs lie at multiples of 16 bytes
+//   tile_rules short      short lists: one sweep, or one for each gate
 //   tile_rules single     gates in sweeps of their own get the list's matrices
 #include <cmath>
 #include <cstddef>
@@ -107,10 +108,57 @@ static int single()
     return differ > 0 ? 0 : 1;                        // (the scale is seen at all)
 }
 
+// Lists of a few gates, each of which touches 2^-controls of the state: whether
+// they share a sweep. The sides are as measured on an MI355X, where one of them
+// is clearly the faster.
+static int short_lists()
+{
+    const struct {
+        int n, gates, controls, rows;
+        bool own_rows, together;
+    } cases[] = {
+        // two gates: 18.5 against 29.4 us, 17.9 : 21.3, 17.0 : 18.3
+        {22, 2, 3, 1, false, false}, {20, 2, 3, 1, false, false}, {10, 2, 3, 1, false, false},
+        // 18.0 : 19.2, 17.4 : 18.9, 7.9 : 6.9 (among others), 17.5 : 16.3
+        {18, 2, 1, 1, false, false}, {16, 2, 1, 1, false, false}, {10, 2, 1, 1, false, true}, {4, 2, 0, 1, false, true},
+        // two CX: 167 : 202, 88 : 100, 47 : 52, 26 : 28.6, 38.8 : 43.7 (behind a reset); 10.3 : 9.1 at 21 qubits
+        {26, 2, 1, 1, false, false}, {25, 2, 1, 1, false, false}, {24, 2, 1, 1, false, false}, {23, 2, 1, 1, false, false},
+        {22, 2, 1, 1, false, false}, {21, 2, 1, 1, false, true},
+        // three CX: 249 : 203, 23.3 : 14.5, 9.5 : 6.8; three with three controls 9.9 : 16.2 on 22
+        {26, 3, 1, 1, false, true}, {22, 3, 1, 1, false, true}, {12, 3, 1, 1, false, true}, {22, 3, 3, 1, false, false},
+        {21, 3, 3, 1, false, false},
+        // without controls: 321 : 198, 26 : 14, 12.8 : 8.5
+        {26, 2, 0, 1, false, true}, {22, 2, 0, 1, false, true}, {20, 2, 0, 1, false, true},
+        // matrices per row take a launch per row
+        {12, 2, 0, 8, true, true}, {14, 2, 2, 3, true, true}, {20, 3, 1, 8, true, true},
+        // long lists
+        {26, 40, 3, 1, false, true}};
+    const sv::cd u[4] = {0.8, sv::cd(0.0, -0.6), sv::cd(0.0, -0.6), 0.8};
+    for (const auto& k : cases) {
+        sv::TileList list;
+        std::vector<sv::cd> ms;
+        for (int r = 0; r < (k.own_rows ? k.rows : 1); ++r) ms.insert(ms.end(), u, u + 4);
+        for (int i = 0; i < k.gates; ++i) {
+            const int target = i % 3, controls[3] = {k.n - 1, k.n - 2, k.n - 3};
+            sv::tile_append(list, 1, &target, k.controls, controls, ms.data(), k.own_rows ? k.rows : 1, i);
+        }
+        sv::TilePlannerHandle plan(list, k.n, k.rows);
+        sv::TileSweep w;
+        if (!plan.next(w) || (int)w.gates.size() != k.gates) return 1;
+        if (w.single == k.together) {
+            std::printf("%d qubits, %d rows, %d gates with %d controls: %s\n", k.n, k.rows, k.gates, k.controls,
+                        w.single ? "a sweep each" : "one sweep");
+            return 1;
+        }
+    }
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     if (argc != 2) return 2;
     if (!std::strcmp(argv[1], "layout")) return layout();
+    if (!std::strcmp(argv[1], "short")) return short_lists();
     if (!std::strcmp(argv[1], "single")) return single();
     return 2;
 }
