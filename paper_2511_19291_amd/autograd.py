@@ -101,6 +101,32 @@ def _forward(state, circuit, p, fuse: bool) -> None:
 # 9.9. The VALU blocks stay available through ``block_qubits``.
 MFMA_MIN_QUBITS = 13
 TILE_GENERAL_MAX_QUBITS = 20
+TILE_MIXED_MAX_QUBITS = 23
+
+
+def _blocks_pay(circuit, width: float) -> bool:
+    """Whether matrix-core blocks beat tiles on a state of 2^width amplitudes
+    (24 and more) where not every parameter is a plain rotation's. Tiles pay
+    per gate: 1 a rotation, 2.5 a general or a controlled gate with a
+    parameter, 1.4 a CNOT or SWAP, 0.6 any other fixed gate. Blocks pay per
+    block, 15 of these at 24 qubits and one less per qubit down to 12.5, and
+    one block takes 3.3 gates on several qubits (bricks and ladders of 4 and 8
+    layers). Training steps, tiles against blocks: bricks with controlled
+    rotations at 24 / 25 / 27 qubits 7.4 / 14.0 / 30.6 ms against 6.7 / 10.9 /
+    21.8, ladders of them 4.5 / 9.0 / 36.0 against 6.5 / 10.9 / 39.3; bricks with
+    CNOTs and a quarter of U3 3.0 / 5.5 / 23.6 against 3.9 / 6.5 / 21.7."""
+    tiles, several, mixed = 0.0, 0, False
+    for op in circuit.ops:
+        wide = len(op.targets) + len(op.controls) > 1
+        several += wide
+        if not op.params:
+            tiles += 1.4 if wide else 0.6
+        elif wide or op.kind not in ("rx", "ry", "rz"):
+            tiles += 2.5
+            mixed = True
+        else:
+            tiles += 1.0
+    return mixed and tiles > max(several / 3.3, circuit.n / 4) * max(39.0 - width, 12.5)
 
 
 def default_block_qubits(circuit, batch: int = 1) -> int:
@@ -111,7 +137,10 @@ def default_block_qubits(circuit, batch: int = 1) -> int:
         return 0
     if any(op.params and len(op.targets) > 1 for op in circuit.ops):
         return sv.ADJOINT_MFMA
-    if circuit.n + np.log2(max(int(batch), 1)) > TILE_GENERAL_MAX_QUBITS and _mostly_general(circuit):
+    width = circuit.n + np.log2(max(int(batch), 1))
+    if width > TILE_GENERAL_MAX_QUBITS and _mostly_general(circuit):
+        return sv.ADJOINT_MFMA
+    if width > TILE_MIXED_MAX_QUBITS and _blocks_pay(circuit, width):
         return sv.ADJOINT_MFMA
     return 0
 
