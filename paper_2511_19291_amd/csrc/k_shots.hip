@@ -63,11 +63,6 @@ static_assert(kShotBits - kChunkBits <= 6, "a lane per chunk");
 constexpr int kSubBits = 4;
 constexpr int kSubMaxBits = 30;
 
-bool keeps_subs(int n, int64_t shots)
-{
-    return n >= kChunkBits && n <= kSubMaxBits && shots >= ((int64_t)1 << n) / 880;
-}
-
 // 1. probability mass of each block of 2^bb amplitudes (bb <= kShotBits).
 // Blocks of at least 128 amplitudes (k_chunk_mass): one workgroup of eight
 // waves per block (2^12 amplitudes: 32 chunks of 128), wave w reading chunks
@@ -954,12 +949,17 @@ int shot_block_bits(int n) { return n < kShotBits ? n : kShotBits; }
 
 }  // namespace
 
-size_t shot_scratch_bytes(int n, int64_t shots)
+bool shot_keeps_subs(int n, int64_t shots)
+{
+    return n >= kChunkBits && n <= kSubMaxBits && shots >= ((int64_t)1 << n) / 880;
+}
+
+size_t shot_scratch_bytes(int n, int64_t shots, bool subs)
 {
     const uint64_t nb = 1ull << (n - shot_block_bits(n));
     const uint64_t st = scan_tmp(nb);
     const uint64_t nch = (uint64_t)nb << (kShotBits - kChunkBits);   // chunk slots
-    const uint64_t nsub = keeps_subs(n, shots) ? nb << (kShotBits - kSubBits) : 0;
+    const uint64_t nsub = subs ? nb << (kShotBits - kSubBits) : 0;
     return (nb + st) * sizeof(double)                 // scanned masses + scan totals
            + nsub * sizeof(double)                    // sums of 16
            + (3 * nb + st) * sizeof(uint32_t)         // counts, fill, (count scan totals)
@@ -989,9 +989,7 @@ void launch_sample_exact(const ShotLaunch& a, hipStream_t st)
     uint32_t* order = reinterpret_cast<uint32_t*>(take((size_t)a.shots * sizeof(uint32_t)));
     const uint64_t nch = nb << (kShotBits - kChunkBits);
     double* csum = reinterpret_cast<double*>(take(nch * sizeof(double)));
-    double* sub = keeps_subs(a.n, a.shots)
-                      ? reinterpret_cast<double*>(take((nb << (kShotBits - kSubBits)) * sizeof(double)))
-                      : nullptr;
+    double* sub = a.subs ? reinterpret_cast<double*>(take((nb << (kShotBits - kSubBits)) * sizeof(double))) : nullptr;
 
     if (bb >= kChunkBits)
         hipLaunchKernelGGL(k_chunk_mass, dim3((unsigned)nb), dim3(kMassThreads), 0, st, a.psi, bb, mass, csum, sub);

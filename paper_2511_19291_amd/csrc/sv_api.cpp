@@ -142,9 +142,10 @@ void check_not_capturing(hipStream_t st)
 
 // ------------------------------------------------------------ scratch
 
-void ensure_scratch(sv_state s, uint64_t doubles)
+// false: there is no memory for it (and the scratch is gone)
+bool try_scratch(sv_state s, uint64_t doubles)
 {
-    if (doubles <= s->scratch_cap) return;
+    if (doubles <= s->scratch_cap) return true;
     if (s->scratch) {
         SV_HIP(hipStreamSynchronize(s->stream));
         SV_HIP(hipFree(s->scratch));
@@ -154,9 +155,15 @@ void ensure_scratch(sv_state s, uint64_t doubles)
     if (hipMalloc(&s->scratch, doubles * sizeof(double)) != hipSuccess) {
         (void)hipGetLastError();
         s->scratch = nullptr;
-        fail(SV_ERR_OUT_OF_MEMORY, "reduction scratch allocation failed");
+        return false;
     }
     s->scratch_cap = doubles;
+    return true;
+}
+
+void ensure_scratch(sv_state s, uint64_t doubles)
+{
+    need(try_scratch(s, doubles), SV_ERR_OUT_OF_MEMORY, "reduction scratch allocation failed");
 }
 
 void ensure_dout(sv_state s, uint64_t doubles)
@@ -1699,9 +1706,18 @@ sv_status sv_sample_exact(sv_state s, int row, const double* dev_uniforms, int64
         need(n_shots >= 0 && n_shots <= 2147483647ll, SV_ERR_INVALID_ARGUMENT, "n_shots must be 0..2^31-1");
         need(n_shots == 0 || (dev_uniforms != nullptr && dev_out != nullptr), SV_ERR_INVALID_ARGUMENT,
              "NULL device pointer");
-        const size_t bytes = shot_scratch_bytes(s->n, n_shots);
-        ensure_scratch(s, (bytes + sizeof(double) - 1) / sizeof(double));
+        auto doubles = [&](bool subs) { return (shot_scratch_bytes(s->n, n_shots, subs) + sizeof(double) - 1) / sizeof(double); };
+        // the sums of 16 take 1/16 of the state: only where there is memory for
+        // them, and on a capturing stream only memory that is already there
+        bool subs = shot_keeps_subs(s->n, n_shots);
+        if (subs && doubles(true) > s->scratch_cap) {
+            hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+            SV_HIP(hipStreamIsCapturing(s->stream, &cs));
+            subs = cs == hipStreamCaptureStatusNone && try_scratch(s, doubles(true));
+        }
+        if (!subs) ensure_scratch(s, doubles(false));
         ShotLaunch a{};
+        a.subs = subs;
         a.psi = s->psi + (uint64_t)row * s->N;
         a.n = s->n;
         a.u = dev_uniforms;

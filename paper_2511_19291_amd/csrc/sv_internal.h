@@ -143,9 +143,12 @@ struct ShotLaunch {
     const double* u;          // device uniforms [shots]
     int64_t shots;
     int64_t* out;             // device indices [shots]
-    void* scratch;            // shot_scratch_bytes(n, shots) bytes
+    bool subs;                // keep the sums of 16 amplitudes
+    void* scratch;            // shot_scratch_bytes(n, shots, subs) bytes
 };
-size_t shot_scratch_bytes(int n, int64_t shots);
+// Whether the sums pay; the indices are the same with and without.
+bool shot_keeps_subs(int n, int64_t shots);
+size_t shot_scratch_bytes(int n, int64_t shots, bool subs);
 void launch_sample_exact(const ShotLaunch& a, hipStream_t st);
 
 // <Z_i> estimates from n_shots drawn indices (-1 = no index): est[n] device
