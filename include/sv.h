@@ -624,21 +624,21 @@ sv_status sv_sweep_order_tune(sv_state s, float* ms_out);
 sv_status sv_sweep_order_set(sv_state s, uint64_t xcd_mask);
 sv_status sv_sweep_order_get(sv_state s, uint64_t* xcd_mask);
 
-/* One way of applying a circuit: plain per-gate sweeps (max_k = 1, mode =
+/* One way of applying a circuit: its gate list with sv_run (max_k = 1, mode =
  * -1) or the fusion planner's blocks of at most max_k qubits applied with
  * sv_apply_fused in `mode`. */
 typedef struct sv_fusion_choice {
     int32_t max_k;
     int32_t mode;
-    int32_t n_sweeps;         /* gates (plain) or blocks: passes over the state */
+    int32_t n_sweeps;         /* passes over the state: launches, of one or more gates or blocks each */
     double ms;                /* time of one application of the whole circuit */
 } sv_fusion_choice;
 
 /* Autotuner of the fusion width: times the circuit (host params, the same
- * for every row) on the state s as plain sweeps, as SV_FUSED_VALU blocks of
+ * for every row) on the state s as a gate list, as SV_FUSED_VALU blocks of
  * max_k = 2..5, (n >= 10) as five-qubit matrix-core blocks in the modes that
  * mode_mask allows, and (12 <= n <= 32, BF16X3 allowed) as six-qubit blocks
- * (bit 1 << SV_FUSED_* of mode_mask; plain sweeps are always tried), and
+ * (bit 1 << SV_FUSED_* of mode_mask; the list is always tried), and
  * returns the fastest. The state's contents are overwritten (reset it
  * afterwards). A width that some gate of the circuit exceeds is skipped.
  *   reps: timed applications per candidate (after one warm-up).

@@ -256,13 +256,13 @@ sv_status sv_fused_autotune(sv_state s, const sv_op* ops, int n_ops, const doubl
         std::vector<sv_fusion_choice> done;
         Timer tm(s->stream);
 
-        // plain per-gate sweeps
+        // the gate list
         {
             ok_or_throw(sv_run(s, ops, n_ops, params, 0, n_params));
             sv_fusion_choice c{};
             c.max_k = 1;
             c.mode = -1;
-            c.n_sweeps = n_ops;
+            c.n_sweeps = s->sweeps;
             c.ms = tm.time(reps, [&] { ok_or_throw(sv_run(s, ops, n_ops, params, 0, n_params)); });
             done.push_back(c);
         }
@@ -279,7 +279,7 @@ sv_status sv_fused_autotune(sv_state s, const sv_op* ops, int n_ops, const doubl
             sv_fusion_choice c{};
             c.max_k = k;
             c.mode = mode;
-            c.n_sweeps = nb;
+            c.n_sweeps = s->sweeps;
             c.ms = tm.time(reps, [&] { ok_or_throw(sv_apply_fused(s, blocks.data(), nb, mode)); });
             done.push_back(c);
         };

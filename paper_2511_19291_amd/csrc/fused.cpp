@@ -632,6 +632,7 @@ sv_status apply_fused_impl(sv_state s, const sv_block* blocks, int n_blocks, int
             sweeps = plan_fused_sweeps(s->n, masks, alone, mode == SV_FUSED_BF16X3);
         else
             for (int i = 0; i < n_blocks; ++i) sweeps.push_back(FusedSweep{0, {i}});
+        s->sweeps = (int)sweeps.size();
         for (const FusedSweep& w : sweeps) {
             const int i = w.blocks[0];
             unsigned char* p = dev + off[i];

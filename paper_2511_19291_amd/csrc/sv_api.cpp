@@ -595,6 +595,7 @@ sv_status sv_run(sv_state s, const sv_op* ops, int n_ops, const double* params, 
         };
         if (n_ops < 2 || !tile_applies(s->n)) {
             for (int i = 0; i < n_ops; ++i) one_gate(i);
+            s->sweeps = n_ops;
             return;
         }
         TileList list;
@@ -606,7 +607,7 @@ sv_status sv_run(sv_state s, const sv_op* ops, int n_ops, const double* params, 
             tile_append(list, info[i].k, ops[i].targets, ops[i].n_controls, ops[i].controls, ms.data(), nm, i);
         }
         // a gate in a sweep of its own: the same matrix as in a program
-        tile_run(all_rows(s), s->n, list, s->stream, [&](const TileGate& g) {
+        s->sweeps = tile_run(all_rows(s), s->n, list, s->stream, [&](const TileGate& g) {
             cd m[16];
             for (int r = 0; r < (g.per_row ? s->batch : 1); ++r) {
                 tile_matrix(list, g, r, m);

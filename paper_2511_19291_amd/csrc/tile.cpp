@@ -948,7 +948,7 @@ void emit_rounds(Emitter& em, int n, const TileList& l, const std::vector<int>& 
 
 }  // namespace
 
-void tile_sweep(const Rows& rows, int n, const TileList& l, const TileSweep& s, hipStream_t st)
+int tile_sweep(const Rows& rows, int n, const TileList& l, const TileSweep& s, hipStream_t st)
 {
     // Few workgroups: half as many amplitudes per thread, so that a compute unit
     // holds twice the waves of its one or two tiles (20-qubit brickwork,
@@ -956,10 +956,15 @@ void tile_sweep(const Rows& rows, int n, const TileList& l, const TileSweep& s, 
     // instead of 904, from the rounds over three bits instead of four).
     const uint64_t groups = (1ull << (n - tile_bits(n))) * rows.nrows;
     const int R = groups <= 2 * (uint64_t)device_info().cu_count ? kTileRegBits - 1 : kTileRegBits;
+    int launches = 0;
     Emitter em(rows, n, l, s.qubits, R,
-               [&](const TileArgs& a, int nr, const std::vector<int>&, bool) { launch_tile(a, nr, R, st); });
+               [&](const TileArgs& a, int nr, const std::vector<int>&, bool) {
+                   launch_tile(a, nr, R, st);
+                   launches += a.row0 == 0;
+               });
     emit_rounds(em, n, l, s.gates, s.qubits, R);
     em.flush();
+    return launches;
 }
 
 bool tile_adjoint_applies(int n) { return n >= kTileRegBits; }

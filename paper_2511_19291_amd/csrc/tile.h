@@ -219,9 +219,10 @@ bool tile_apart(const TileList& l, const int* gates, int count, int n, int rows)
 void tile_matrix(const TileList& l, const TileGate& g, int r, cd* m);
 
 // Apply the list to every row, asynchronously on `st`. Gates that a sweep of
-// their own serves better are handed to one_gate(gate), or one_gate(op).
+// their own serves better are handed to one_gate(gate), or one_gate(op). Returns
+// the number of launches over the state (a row's, where rows take several).
 template <class F>
-void tile_run(const Rows& rows, int n, const TileList& l, hipStream_t st, const F& one_gate);
+int tile_run(const Rows& rows, int n, const TileList& l, hipStream_t st, const F& one_gate);
 
 bool tile_applies(int n);
 
@@ -240,7 +241,8 @@ struct TilePlannerHandle {
     TilePlannerHandle& operator=(const TilePlannerHandle&) = delete;
     bool next(TileSweep& s);
 };
-void tile_sweep(const Rows& rows, int n, const TileList& l, const TileSweep& s, hipStream_t st);
+// (returns its launches: a program longer than the kernel arguments takes more)
+int tile_sweep(const Rows& rows, int n, const TileList& l, const TileSweep& s, hipStream_t st);
 
 // The adjoint of a list (the circuit's U^* from last to first, derivatives
 // marked) on states of 4..12 qubits: queues the launches that write every
@@ -264,7 +266,7 @@ void tile_adjoint_sweep(float2* psi, float2* lam, int n, int rows, const TileLis
                         double* out, std::vector<TileValues>& values, hipStream_t st);
 
 template <class F>
-void tile_run(const Rows& rows, int n, const TileList& l, hipStream_t st, const F& one_gate)
+int tile_run(const Rows& rows, int n, const TileList& l, hipStream_t st, const F& one_gate)
 {
     auto one = [&](const TileGate& g) {
         if constexpr (std::is_invocable_v<F, const TileGate&>) one_gate(g);
@@ -273,16 +275,20 @@ void tile_run(const Rows& rows, int n, const TileList& l, hipStream_t st, const 
     // a few gates: what the planner would find, without its 0.5 us
     if (l.gates.size() <= 3 && tile_apart(l, nullptr, (int)l.gates.size(), n, rows.nrows)) {
         for (const TileGate& g : l.gates) one(g);
-        return;
+        return (int)l.gates.size();
     }
     TilePlannerHandle plan(l, n, rows.nrows);
     TileSweep s;
+    int launches = 0;
     while (plan.next(s)) {
-        if (s.single)
+        if (s.single) {
             for (int g : s.gates) one(l.gates[g]);
-        else
-            tile_sweep(rows, n, l, s, st);
+            launches += (int)s.gates.size();
+        } else {
+            launches += tile_sweep(rows, n, l, s, st);
+        }
     }
+    return launches;
 }
 
 }  // namespace sv
