@@ -15,7 +15,7 @@ kernel (the dense one-qubit sweep, timed live with HIP events on the state's
 stream over the timed region) against 8 TB/s and against the copy ceiling
 measured in the same run, the error of every reported result against the
 complex128 oracle's stored values (tests/golden), the fused-MFMA / adjoint /
-batched forms as speedups over the plain form on the same GPU (parameter
+batched forms as speedups on the same GPU, each named by its base (parameter
 shift measured on 16 parameters and scaled), and the CPU oracle timed on
 bounded samples of this and the other workloads.
 
@@ -333,8 +333,26 @@ def _timed_ms(fn, stream) -> float:
     return e0.elapsed_time(e1)
 
 
-def extras(args, n, plain_gates_per_s, avg_dense_ms, copy_GBps) -> dict:
-    """Fused-MFMA, adjoint and batched forms against the plain form, each on
+def fused_entry(ms, n_gates, n_blocks, nq) -> dict:
+    """One fused form of a circuit: its time, and what follows from it whatever
+    number of blocks share a sweep (a rate of memory per block does not)."""
+    per_block = ms / n_blocks
+    return {"ms": round(ms, 2), "gates_per_s": round(n_gates / (ms / 1e3), 1), "ms_per_block": round(per_block, 4),
+            "TFLOPs": round(8 * 32 * (1 << nq) / (per_block / 1e3) / 1e12, 2)}
+
+
+def fused_speedups(entry) -> None:
+    """Speedups of the fused forms, each under the name of what it is against:
+    the circuit as one gate list (several gates per sweep), and gate by gate
+    (a sweep each) where that was timed."""
+    for name in ("fp32_mfma", "bf16x3", "bf16x3_k6"):
+        for base in ("gate_list", "gate_by_gate"):
+            if f"{base}_ms" in entry:
+                entry[name][f"speedup_vs_{base}"] = round(entry[f"{base}_ms"] / entry[name]["ms"], 2)
+
+
+def extras(args, n, gate_by_gate_per_s, avg_dense_ms, copy_GBps) -> dict:
+    """Fused-MFMA, adjoint and batched forms against gate lists, each on
     its own workload, all on this GPU."""
     import numpy as np
     import torch
@@ -374,7 +392,7 @@ def extras(args, n, plain_gates_per_s, avg_dense_ms, copy_GBps) -> dict:
 
     # -- fused blocks: the same 30-qubit brickwork, and the 32-qubit instance
     fused = {}
-    for nq, seed, with_plain in ((n, 2, False), (32, 3, True)):
+    for nq, seed in ((n, 2), (32, 3)):
         circ = C.brickwork_u3_cz(nq, 20, seed)
         t0 = time.perf_counter()
         blocks = sv.fuse_plan(circ, 5)
@@ -386,12 +404,7 @@ def extras(args, n, plain_gates_per_s, avg_dense_ms, copy_GBps) -> dict:
             st.reset()
             st.apply_fused(blocks[:2], mode)
             ms = _timed_ms(lambda: (st.reset(), st.apply_fused(blocks, mode)), stream)
-            per_block = ms / len(blocks)
-            gbps = 16 * (1 << nq) / (per_block / 1e3) / 1e9
-            entry[name] = {"ms": round(ms, 2), "gates_per_s": round(len(circ.ops) / (ms / 1e3), 1),
-                           "ms_per_block": round(per_block, 4),
-                           "GBps_per_block": round(gbps, 1), "frac_of_copy_per_block": round(gbps / copy_GBps, 3),
-                           "TFLOPs_per_block": round(8 * 32 * (1 << nq) / (per_block / 1e3) / 1e12, 2)}
+            entry[name] = fused_entry(ms, len(circ.ops), len(blocks), nq)
             zs[name] = st.expval_z_all()[0]          # the state holds this mode's output
             if nq == 30:
                 entry[name]["error_vs_oracle"] = error_vs_golden_z("brickwork30", nq, zs[name])
@@ -406,26 +419,24 @@ def extras(args, n, plain_gates_per_s, avg_dense_ms, copy_GBps) -> dict:
         zs["bf16x3_k6"] = st.expval_z_all()[0]
         if nq == 30:
             entry["bf16x3_k6"]["error_vs_oracle"] = error_vs_golden_z("brickwork30", nq, zs["bf16x3_k6"])
-        if with_plain:
-            table = sv.OpTable(circ.ops)
-            p = np.ascontiguousarray(circ.params)
-            ms = _timed_ms(lambda: (st.reset(), st.run_ops(table, 0, len(circ.ops), p)), stream)
-            entry["plain_ms"] = round(ms, 2)
-            zp = st.expval_z_all()[0]
-            # no oracle state at 32 qubits (32 GiB of complex64, 64 GiB in complex128): against the plain sweeps
-            for name in ("fp32_mfma", "bf16x3", "bf16x3_k6"):
-                entry[name]["max_abs_z_i_vs_plain"] = float(np.max(np.abs(zs[name][:nq] - zp[:nq])))
+        table = sv.OpTable(circ.ops)
+        p = np.ascontiguousarray(circ.params)
+        entry["gate_list_ms"] = round(_timed_ms(lambda: (st.reset(), st.run_ops(table, 0, len(circ.ops), p)), stream), 2)
+        if nq == n:
+            entry["gate_by_gate_ms"] = round(len(circ.ops) / gate_by_gate_per_s * 1e3, 2)
         else:
-            entry["plain_ms"] = round(len(circ.ops) / plain_gates_per_s * 1e3, 2)
-        for name in ("fp32_mfma", "bf16x3", "bf16x3_k6"):
-            entry[name]["speedup_vs_plain"] = round(entry["plain_ms"] / entry[name]["ms"], 2)
+            # no oracle state at 32 qubits (32 GiB of complex64, 64 GiB in complex128): against the gate list
+            zp = st.expval_z_all()[0]
+            for name in ("fp32_mfma", "bf16x3", "bf16x3_k6"):
+                entry[name]["max_abs_z_i_vs_gate_list"] = float(np.max(np.abs(zs[name][:nq] - zp[:nq])))
+        fused_speedups(entry)
         if nq == n:
             # fusion width and arithmetic picked by the library's autotuner
-            # (plain sweeps, vector blocks of k = 2..5, matrix-core blocks)
+            # (the gate list, vector blocks of k = 2..5, matrix-core blocks)
             t0 = time.perf_counter()
             best, trials = sv.fused_autotune(st, circ, modes=(sv.FUSED_FP32_MFMA, sv.FUSED_BF16X3, sv.FUSED_VALU),
                                              reps=1)
-            names = {-1: "plain", sv.FUSED_FP32_MFMA: "fp32_mfma", sv.FUSED_BF16X3: "bf16x3", sv.FUSED_VALU: "valu"}
+            names = {-1: "gate_list", sv.FUSED_FP32_MFMA: "fp32_mfma", sv.FUSED_BF16X3: "bf16x3", sv.FUSED_VALU: "valu"}
             entry["autotune"] = {
                 "chosen": {"max_k": best["max_k"], "mode": names[best["mode"]], "ms": round(best["ms"], 2),
                            "sweeps": best["n_sweeps"]},
@@ -477,10 +488,10 @@ def extras(args, n, plain_gates_per_s, avg_dense_ms, copy_GBps) -> dict:
     n_par = circ.n_params
     # parameter shift measured on the GPU for 16 seeded parameters (two
     # forwards and one <Z> reduction each), scaled to all parameters; once
-    # with plain sweeps, once with the fused forward
+    # with the gate list, once with the fused forward
     which = np.random.default_rng(28).choice(n_par, size=16, replace=False)
     shift = {}
-    for fwd in ("plain", "fused"):
+    for fwd in ("gate_list", "fused"):
         vals = []
         torch.cuda.synchronize()
         t0 = time.perf_counter()
@@ -490,7 +501,7 @@ def extras(args, n, plain_gates_per_s, avg_dense_ms, copy_GBps) -> dict:
                 prm = circ.params.copy()
                 prm[q] += sgn * np.pi / 2
                 st.reset()
-                if fwd == "plain":
+                if fwd == "gate_list":
                     st.run_ops(table, 0, len(circ.ops), np.ascontiguousarray(prm))
                 else:
                     st.run_fused(circ, prm)
@@ -501,7 +512,7 @@ def extras(args, n, plain_gates_per_s, avg_dense_ms, copy_GBps) -> dict:
                       "max_abs_vs_adjoint": float(np.max(np.abs(np.array(vals) - grad[0][which])))}
     # the autograd layers' defaults for this circuit: forward and backward in
     # tiles (several gates per sweep)
-    shift_ms = shift["plain"]["ms_scaled_to_all"]
+    shift_ms = shift["gate_list"]["ms_scaled_to_all"]
     default_ms = bwd_ms
     res["adjoint"] = {
         "workload": "rxry_ring28: 28 qubits, 10 x [RX all, RY all, CNOT ring], loss <sum Z_i>",
@@ -512,10 +523,10 @@ def extras(args, n, plain_gates_per_s, avg_dense_ms, copy_GBps) -> dict:
         "backward_over_forward": round(default_ms / fwd_ms, 3),
         "backward_per_gate_ms": round(bwd_ms, 2), "per_gate_over_forward": round(bwd_ms / fwd_ms, 3),
         "param_shift": {"measured": "16 seeded parameters on this GPU, two forwards + <sum Z> each, "
-                                    "scaled to all parameters", "plain_forward": shift["plain"],
+                                    "scaled to all parameters", "gate_list_forward": shift["gate_list"],
                         "fused_forward": shift["fused"]},
         "speedup_vs_param_shift": round(shift_ms / default_ms, 1),
-        "speedup_basis": "parameter shift with the plain forward (scaled from 16 parameters) / tiled backward",
+        "speedup_basis": "parameter shift with the gate-list forward (scaled from 16 parameters) / tiled backward",
         # bytes of one sweep per gate (32 B/amplitude per rotation, 16 per
         # CNOT) over the backward's time: an
         # effective rate, not an HBM fraction
@@ -992,7 +1003,7 @@ def run_pmc_probe(n: int) -> int:
 
 
 def run_adjoint_probe(n: int) -> int:
-    """One forward (plain sweeps) and one matrix-core adjoint backward of the
+    """One forward (the gate list) and one matrix-core adjoint backward of the
     n-qubit ring of 10 RX/RY layers with CNOT rings, loss <sum Z_i>."""
     import torch
 
