@@ -348,7 +348,12 @@ std::vector<FusedSweep> plan_fused_sweeps(int n, const std::vector<uint64_t>& ma
 }
 
 // The words of a block on the tile: of its eight column bits five that reach
-// all banks of LDS, if there are such, first.
+// all banks of LDS, if there are such, first. A block of fewer than five qubits is
+// padded with the lowest others, where its matrix is the identity. Those below 4
+// are in every tile; a block within qubits 0..3 is padded with qubit 4 too, and
+// where the tile has no qubit 4, its tile bit is the next higher qubit's, which
+// the block does not touch either: any bit does for an identity, as long as the
+// five differ.
 void fused_tile_block(uint64_t tile, const int* targets, uint32_t at, uint32_t* w)
 {
     uint32_t row[5], rows = 0;
@@ -357,6 +362,7 @@ void fused_tile_block(uint64_t tile, const int* targets, uint32_t at, uint32_t* 
         rows |= bit;
         row[j] = 8u * fused_tile_place(bit);
     }
+    need(__builtin_popcount(rows) == 5, SV_ERR_INVALID_ARGUMENT, "a block's tile bits coincide");
     uint32_t col[8], part[3], span[5] = {};
     int nc = 0, np = 0;
     std::vector<uint32_t> rest;
