@@ -8,19 +8,14 @@ import subprocess
 
 import pytest
 
-from tests.test_sanitized_host import HIPCC, _device_objects
-
-HERE = os.path.dirname(os.path.abspath(__file__))
+from tests import host_build
 
 
 def test_one_limit_per_kernel(tmp_path):
-    if not os.path.exists(HIPCC):
+    if not os.path.exists(host_build.HIPCC):
         pytest.skip("hipcc not found")
-    objs = [o for o in _device_objects() if os.path.basename(o) in ("k_tile_adj.hip.o", "k_batch.hip.o")]
+    objs = [o for o in host_build.library_objects() if os.path.basename(o) in ("k_tile_adj.hip.o", "k_batch.hip.o")]
     exe = str(tmp_path / "lds_limit")
-    cmd = [HIPCC, "-O1", "-std=c++17", "--offload-arch=gfx950", os.path.join(HERE, "lds_limit.cpp"), "-x", "none",
-           *objs, "-o", exe]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    assert r.returncode == 0, r.stderr
+    host_build.build(exe, "lds_limit.cpp", objs)
     r = subprocess.run([exe], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout + r.stderr

@@ -2,18 +2,13 @@
 own host code, HIP's calls replaced (tests/sweep_counts.cpp, tests/fake_hip.h)."""
 
 import os
-import subprocess
 
 import pytest
 
-from tests.test_sanitized_host import HIPCC
-from tests.test_shot_scratch import build_with_library
+from tests import host_build
 
 
 def test_n_sweeps_counts_passes(tmp_path):
-    if not os.path.exists(HIPCC):
+    if not os.path.exists(host_build.HIPCC):
         pytest.skip("hipcc not found")
-    exe = str(tmp_path / "sweep_counts")
-    build_with_library(exe, "sweep_counts.cpp")
-    r = subprocess.run([exe], capture_output=True, text=True)
-    assert r.returncode == 0, r.stdout + r.stderr
+    host_build.run_with_library(str(tmp_path / "sweep_counts"), "sweep_counts.cpp")
