@@ -1713,8 +1713,10 @@ sv_status sv_sample_exact(sv_state s, int row, const double* dev_uniforms, int64
         bool subs = shot_keeps_subs(s->n, n_shots);
         if (subs && doubles(true) > s->scratch_cap) {
             hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-            SV_HIP(hipStreamIsCapturing(s->stream, &cs));
-            subs = cs == hipStreamCaptureStatusNone && try_scratch(s, doubles(true));
+            // (an error: the default stream, while another captures)
+            const bool plain = hipStreamIsCapturing(s->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone;
+            if (!plain) (void)hipGetLastError();
+            subs = plain && try_scratch(s, doubles(true));
         }
         if (!subs) ensure_scratch(s, doubles(false));
         ShotLaunch a{};
