@@ -663,7 +663,7 @@ sv_status sv_expval_pauli(sv_state s, const sv_pauli_term* terms, int n_terms, d
                 x[t] = terms[t].x_mask;
                 z[t] = terms[t].z_mask;
             }
-            plan_pauli_tiles(s->n, x.data(), z.data(), n_terms, sweeps, rest);
+            plan_pauli_tiles(s->n, s->batch, x.data(), z.data(), n_terms, sweeps, rest);
         } else {
             for (int t = 0; t < n_terms; ++t) rest.push_back(t);
         }

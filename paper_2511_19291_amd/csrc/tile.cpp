@@ -1069,7 +1069,7 @@ void tile_adjoint_sweep(float2* psi, float2* lam, int n, int rows, const TileLis
 
 bool pauli_tile_applies(int n) { return n >= 4; }
 
-void plan_pauli_tiles(int n, const uint64_t* x, const uint64_t* z, int count, std::vector<PauliSweep>& sweeps,
+void plan_pauli_tiles(int n, int rows, const uint64_t* x, const uint64_t* z, int count, std::vector<PauliSweep>& sweeps,
                       std::vector<int>& rest)
 {
     // runs of 2^4 amplitudes (whole 128-byte lines) leave the tile eight
@@ -1102,8 +1102,21 @@ void plan_pauli_tiles(int n, const uint64_t* x, const uint64_t* z, int count, st
         // One sweep by x (at most 8 strings) does as well for one string, and
         // for one x below 20 qubits, where the launch is all: 19.6 us against
         // 20.2 at 8 qubits for a string, 21.5 against 23.3 for 8; at 20 qubits
-        // 8 strings take 32.2 and 24.9, at 28 qubits 754 and 438.
-        if (take.size() == 1 || (n < 20 && take.size() <= 8 && x[take.front()] == x[take.back()])) {
+        // 8 strings take 32.2 and 24.9, at 28 qubits 754 and 438. Nor do a few
+        // strings pay for a workgroup and its tile on each of thousands of small
+        // rows: a row costs the tile 2.4 ns more than it costs a sweep by x, and
+        // each of these 5 us and 0.3 ns a row; both read the rows, once or each
+        // time (60000 rows of 6 qubits, 2 / 3 / 8 strings of as many x: 276 /
+        // 389 / 1006 us by x, 367 / 480 / 996 in one tile sweep; 8000 rows 66 /
+        // 87 / 216 and 74 / 92 / 162).
+        int by_x = 0;                 // sweeps by x
+        for (size_t k = 0, same = 0; k < take.size(); ++k) {
+            same = k && x[take[k]] == x[take[k - 1]] ? same + 1 : 0;
+            by_x += same % 8 == 0;
+        }
+        const double read = 8.0 * (double)(1ull << n) / 8.0e6;       // us a row
+        if (take.size() == 1 || (n < 20 && take.size() <= 8 && by_x == 1) ||
+            (take.size() <= 8 && by_x > 1 && 5.0 + rows * (2.4e-3 + read) > by_x * (5.0 + rows * (0.3e-3 + read)))) {
             rest.insert(rest.end(), take.begin(), take.end());
             continue;
         }

@@ -172,13 +172,13 @@ void launch_pauli_tile(const PauliTileArgs& a, int rows, double* out, hipStream_
 // Strings (x, z) for every row, grouped into sweeps: out receives rows *
 // (strings of the sweep) doubles per sweep, `order` the strings in that
 // order, one list per sweep. Strings it leaves out (more x bits than a tile
-// holds) are in `rest`.
+// holds, or better off in sweeps by x) are in `rest`.
 struct PauliSweep {
     PauliTileArgs args;
     std::vector<int> terms;
 };
 bool pauli_tile_applies(int n);
-void plan_pauli_tiles(int n, const uint64_t* x, const uint64_t* z, int count, std::vector<PauliSweep>& sweeps,
+void plan_pauli_tiles(int n, int rows, const uint64_t* x, const uint64_t* z, int count, std::vector<PauliSweep>& sweeps,
                       std::vector<int>& rest);
 
 // One gate as the planner sees it. Fixed qubits (`nc` of them) must be 1 for

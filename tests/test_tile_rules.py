@@ -40,3 +40,7 @@ def test_lone_gates_keep_the_lists_matrices(rules):
 
 def test_short_lists_take_the_faster_sweeps(rules):
     rules("short")
+
+
+def test_few_strings_on_many_rows_go_by_x(rules):
+    rules("strings")

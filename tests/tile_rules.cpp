@@ -2,6 +2,7 @@
 //
 //   tile_rules layout     the programs lie at multiples of 16 bytes
 //   tile_rules short      short lists: one sweep, or one for each gate
+//   tile_rules strings    few strings on many small rows: sweeps by x or tiles
 //   tile_rules single     gates in sweeps of their own get the list's matrices
 #include <cmath>
 #include <cstddef>
@@ -154,11 +155,47 @@ static int short_lists()
     return 0;
 }
 
+// Sets of strings with as many x as strings (or two, or one): whether they go into
+// a tile sweep, as measured on an MI355X where one side is clearly the faster.
+static int strings()
+{
+    const struct {
+        int n, rows, count, xs;
+        bool tiles;
+    } cases[] = {
+        // 276 us by x, 367 in tiles; 389 : 480; 66 : 74
+        {6, 60000, 2, 2, false}, {6, 60000, 3, 3, false}, {6, 8000, 2, 2, false}, {9, 60000, 3, 3, false}, {7, 60000, 5, 5, false}, {4, 60000, 8, 2, false},
+        // 45 : 37, 149 : 125, 2657 : 2236, 28 : 25
+        {6, 1000, 3, 3, true}, {6, 8000, 5, 5, true}, {6, 60000, 20, 20, true}, {6, 100, 2, 2, true},
+        // 1125 : 353; single rows of any width
+        {13, 20000, 3, 3, true}, {8, 1, 2, 2, true}, {12, 1, 3, 3, true}, {24, 1, 2, 2, true},
+        // one x: 21.5 : 23.3 at 8 qubits, 32.2 : 24.9 at 20
+        {8, 1, 8, 1, false}, {20, 1, 8, 1, true}};
+    for (const auto& k : cases) {
+        std::vector<uint64_t> x(k.count), z(k.count);
+        for (int i = 0; i < k.count; ++i) {
+            x[i] = 1 + i % k.xs;
+            z[i] = i / k.xs;
+        }
+        std::vector<sv::PauliSweep> sweeps;
+        std::vector<int> rest;
+        sv::plan_pauli_tiles(k.n, k.rows, x.data(), z.data(), k.count, sweeps, rest);
+        size_t placed = rest.size();
+        for (const auto& w : sweeps) placed += w.terms.size();
+        if (placed != (size_t)k.count || rest.empty() != k.tiles) {
+            std::printf("%d qubits, %d rows, %d strings of %d x: %zu by x\n", k.n, k.rows, k.count, k.xs, rest.size());
+            return 1;
+        }
+    }
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     if (argc != 2) return 2;
     if (!std::strcmp(argv[1], "layout")) return layout();
     if (!std::strcmp(argv[1], "short")) return short_lists();
+    if (!std::strcmp(argv[1], "strings")) return strings();
     if (!std::strcmp(argv[1], "single")) return single();
     return 2;
 }
