@@ -290,7 +290,7 @@ void tile_append(TileList& l, int k, const int* targets, int nc, const int* cont
     g.nc = nc;
     for (int j = 0; j < nc; ++j) g.controls[j] = controls[j];
     g.op = op;
-    g.mat = (int)l.pool.size();
+    g.mat = l.pool.size();
     g.per_row = nm > 1;
     if (diag && ones && !deriv) {
         for (int j = 0; j < k; ++j) g.controls[g.nc++] = targets[j];

@@ -190,7 +190,7 @@ struct TileGate {
     int targets[2];
     int nc;
     int controls[SV_MAX_CONTROLS + 2];
-    int mat;                          // first float of row 0's matrix in the pool
+    size_t mat;                       // first float of row 0's matrix in the pool
     bool per_row;                     // one matrix per row, one after the other
     int deriv;                        // TileDeriv
     int op;                           // the caller's index of the gate

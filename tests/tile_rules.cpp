@@ -37,6 +37,8 @@ static int layout()
 {
     const size_t run = offsetof(sv::TileArgs, words), adj = offsetof(sv::TileAdjArgs, words);
     std::printf("words at %zu and %zu\n", run, adj);
+    // the matrices of a list for every row are found past 2^31 floats (16000 U3 on 16384 rows)
+    if (sizeof(sv::TileGate::mat) < 8) return 1;
     return run % 16 == 0 && adj % 16 == 0 && alignof(sv::TileArgs) % 16 == 0 && alignof(sv::TileAdjArgs) % 16 == 0 ? 0 : 1;
 }
 
