@@ -22,7 +22,8 @@ bounded samples of this and the other workloads.
 Probes for rocprofv3 (short fixed sequences): --pmc-probe (dense gates,
 fused blocks of every form, a plain copy of known size), --adjoint-probe
 (forward + matrix-core backward at --n qubits, then a copy), --shots-probe,
---batch-probe. --summarize turns rocprofv3 CSV output into the summaries
+--batch-probe, --case-probe NAME (three passes of a case of perf/cases.py, then a
+copy). --summarize turns rocprofv3 CSV output into the summaries
 under profiles/ (no GPU needed).
 """
 
@@ -57,6 +58,7 @@ def parse():
                     help="print a profile summary from rocprofv3 CSV output and exit (no GPU): "
                          "stats DIR | traffic FETCH_DIR WRITE_DIR KERNEL_REGEX COPY_BYTES [ALG_BYTES] | "
                          "counters DIR [KERNEL_REGEX]")
+    ap.add_argument("--case-probe", metavar="NAME", help="three passes of a case of perf/cases.py for rocprofv3, then a copy")
     ap.add_argument("--pmc-probe", action="store_true")
     ap.add_argument("--shots-probe", action="store_true",
                     help="the shot-sampling part of the bench alone (n-qubit brickwork output state), for profiles")
@@ -167,6 +169,8 @@ def main() -> int:
         return run_adjoint_probe(n)
     if args.batch_probe:
         return run_batch_probe()
+    if args.case_probe:
+        return run_case_probe(args.case_probe)
     if args.shots_probe:
         circ = C.brickwork_u3_cz(n, 20, 2)
         st = sv.State(n)
@@ -868,7 +872,8 @@ def summarize(argv) -> int:
                                       for the plain copy kernel k_copy of the same run
       counters DIR [RE]               per kernel: median duration, launch shape and counters; with
                                       GRBM_GUI_ACTIVE the clock (busy cycles / 8 XCDs / duration),
-                                      with SQ_VALU_MFMA_BUSY_CYCLES the matrix cores' busy share, and
+                                      with SQ_INSTS_VALU the vector unit's issue share, with
+                                      SQ_VALU_MFMA_BUSY_CYCLES the matrix cores' busy share, and
                                       with SQ_WAVE_CYCLES the shares of wave time at a wait
                                       (SQ_WAIT_ANY) and waiting to issue (SQ_WAIT_INST_ANY)"""
     import statistics
@@ -952,6 +957,9 @@ def summarize(argv) -> int:
             if "GRBM_GUI_ACTIVE" in ctrs:
                 g = med([v["GRBM_GUI_ACTIVE"] for _, v in lst])
                 print(f"  clock GHz (GRBM_GUI_ACTIVE / 8 XCDs / duration): {g / 8 / (ms * 1e6):.2f}")
+                if "SQ_INSTS_VALU" in ctrs:
+                    vi = med([v["SQ_INSTS_VALU"] for _, v in lst])
+                    print(f"  vector issue share (4 cycles an instruction / (1024 SIMDs x cycles)): {4 * vi / (1024 * g / 8):.3f}")
                 if "SQ_VALU_MFMA_BUSY_CYCLES" in ctrs:
                     mb = med([v["SQ_VALU_MFMA_BUSY_CYCLES"] for _, v in lst])
                     print(f"  MFMA busy share at that clock (busy / (1024 SIMDs x cycles)): {mb / (1024 * g / 8):.3f}")
@@ -1042,6 +1050,31 @@ def run_batch_probe() -> int:
         torch.cuda.synchronize()
         print(json.dumps({"batch_probe": True, "config": plan.info()["config"], "stats": plan.stats()}), flush=True)
         plan.free()
+    return 0
+
+
+CASE_PROBE_COPY_BYTES = 1 << 30
+
+
+def run_case_probe(name: str) -> int:
+    """Three passes of one of perf/cases.py's listed cases, then one plain copy of
+    1 GiB (k_copy) to scale byte counters."""
+    import torch
+
+    from paper_2511_19291_amd import sv
+    from perf import cases
+
+    case = next(c for c in cases.listed() if c["name"] == name)
+    s = cases.prepare(case, 1)
+    for _ in range(3):
+        cases.run(s)
+    torch.cuda.synchronize()
+    buf = torch.zeros(2 * CASE_PROBE_COPY_BYTES, dtype=torch.uint8, device="cuda")
+    stream = torch.cuda.current_stream()
+    sv.check(sv.lib().sv_stream_copy(buf.data_ptr() + CASE_PROBE_COPY_BYTES, buf.data_ptr(), CASE_PROBE_COPY_BYTES,
+                                     stream.cuda_stream))
+    torch.cuda.synchronize()
+    print(json.dumps({"case_probe": case}), flush=True)
     return 0
 
 
