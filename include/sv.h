@@ -188,10 +188,14 @@ typedef struct sv_block {
 #define SV_FUSED_BF16X3 1         /* split BF16 (hi + lo) MFMA, 3 products, FP32 accumulation */
 #define SV_FUSED_VALU 2           /* FP32 vector FMAs (no matrix cores) */
 
-/* Apply the blocks in order to every row. Each block is one sweep over the
- * state: the 2^k amplitudes that differ only in the target bits form a
- * column, and the block computes Y = M X over all 2^(n-k) columns (Alg. 1
- * with |Q| = k).
+/* Apply the blocks in order to every row: the 2^k amplitudes that differ only
+ * in a block's target bits form a column, and the block computes Y = M X over
+ * all 2^(n-k) columns (Alg. 1 with |Q| = k). A sweep over the state takes one
+ * block, in the matrix-core modes from 13 qubits on as many blocks of at most
+ * five qubits as share a tile of 2^13 amplitudes. SV_FUSED_BF16X3 keeps the
+ * blocks' order, its results are those of one block after the other to the bit;
+ * in SV_FUSED_FP32_MFMA blocks on different qubits may change places, which
+ * changes the rounding (some 1e-7).
  *   k <= 5: every mode; the matrix-core modes pad the block to five qubits
  *     (M (x) I on the lowest free qubits) and need n >= 10; SV_FUSED_VALU
  *     takes k <= 5 as given.
@@ -280,7 +284,9 @@ sv_status sv_expval_z_all_noalloc(sv_state s, double* dev_out);
  * input is recomputed from its output as x = U^* y (Sec. 4.4):
  *     lam <- O psi;  for l = L..1: psi <- U_l^* psi;
  *     g[p] += 2 Re <lam| dU_l/dtheta_p |psi>;  lam <- U_l^* lam.
- * The inner products are FP64.
+ * The inner products are FP64. From four qubits on, where every parameter is
+ * a one-target gate's, a sweep of both vectors takes a list of gates, as in
+ * sv_run; otherwise each gate takes its own.
  *   grad_out: host [batch][n_params]; loss_out: host [batch] (may be NULL);
  *   drift_out: host [batch] (may be NULL) = || psi_recomputed - e_0 ||, the
  *     distance of the recovered start state from |0..0> (meaningful when the
@@ -343,9 +349,12 @@ sv_status sv_adjoint_grad_blocked(sv_state s, const sv_op* ops, int n_ops, const
  * The running sums are FP64 in a fixed blocking and order (deterministic);
  * they differ from an exact sum by rounding only, so a u_s within ~1e-15
  * (relative) of a CDF step may select the neighbouring index. Work: one read
- * sweep over the row plus one read of each 4096-amplitude block that holds a
- * shot. Scratch device memory (about 12 B per 4096 amplitudes + 16 B per
- * shot) is kept in the state. Asynchronous on the state's stream.
+ * sweep over the row, then per shot its block's chunk masses and 1 KiB; with at
+ * least a shot per 880 amplitudes (7 <= n <= 30) the sweep also keeps the sums
+ * of 16 amplitudes and a shot reads 64 B of these and 128 B of the state.
+ * Scratch device memory (about 280 B per 4096 amplitudes + 16 B per shot; the
+ * sums half a byte per amplitude, left out where there is no memory for them
+ * or, on a capturing stream, not yet) is kept in the state. Asynchronous on the state's stream.
  * Errors: SV_ERR_INVALID_ARGUMENT (row out of range, n_shots outside
  * 0..2^31-1, NULL pointers), SV_ERR_OUT_OF_MEMORY, SV_ERR_HIP. */
 sv_status sv_sample_exact(sv_state s, int row, const double* dev_uniforms, int64_t n_shots,

@@ -2,16 +2,17 @@
 execution, Sec. 4.4 and the `invertible=True` device of Appendix A).
 
 Forward: reset the state to |0..0>, run the circuit with the given
-parameters, return L = sum_t coeff_t <P_t> per batch row. Once
-2n + log2(batch) >= 44 (``fuse``: batch 16 from 20 qubits, batch 1 from 22),
-the gates are fused into 5-qubit blocks on the matrix cores (Sec. 4.1.1);
-runs of per-row gates (an input encoding) with one matrix per row. Backward: the library un-applies the gates from the forward output
-(x = U^* y) and accumulates dL/dtheta in FP64; nothing is stored between the
-passes except the final state itself. By default the backward groups the
-gates into 4-qubit blocks on the matrix cores (``sv_adjoint_grad_mfma``, one
-sweep per block) from 13 qubits when every gate fits; ``block_qubits=0``
-selects the per-gate backward, 3..5 the VALU blocks. The state object
-therefore holds one pending forward at a time: run backward before the next
+parameters, return L = sum_t coeff_t <P_t> per batch row. The gates go as one
+list, several to a sweep of the state; with ``fuse`` (by default for mostly
+general gates once 2n + log2(batch) >= 52) they are fused into 5-qubit blocks on
+the matrix cores (Sec. 4.1.1), runs of per-row gates (an input encoding) with one
+matrix per row. Backward: the library un-applies the gates from the forward
+output (x = U^* y) and accumulates dL/dtheta in FP64; nothing is stored between
+the passes except the final state itself. ``block_qubits=0`` un-applies them
+gate by gate in tiles of state and co-state, ``sv.ADJOINT_MFMA`` in 4-qubit
+blocks on the matrix cores (``sv_adjoint_grad_mfma``, one sweep per block), 3..5
+in VALU blocks; by default whichever of the first two is faster for the circuit's
+gates and width (``default_block_qubits``). The state object therefore holds one pending forward at a time: run backward before the next
 forward on the same state. Every backward checks this: it raises
 ``StaleStateError`` when the state changed after the forward that saved it
 (a second forward on the same state, or a second backward through the same
@@ -63,7 +64,10 @@ def _check_drift(drift) -> None:
 
 def _mostly_general(circuit) -> bool:
     """Whether the circuit has more than a third as many general one-target
-    gates with parameters (U3, phases) as rotations."""
+    gates with parameters (U3, phases) as rotations. (Training steps of 4 layers
+    of bricks, tiles against blocks: a tenth / a fifth / 30 % of U3 on 24 qubits
+    2.8 / 2.8 / 3.0 ms against 3.9, on 26 10.4 / 10.5 / 11.1 against 11.3, U3 only on 22
+    1.46 against 1.21; ``_blocks_pay`` decides what lies between.)"""
     general = sum(1 for op in circuit.ops if op.params and op.kind not in ("rx", "ry", "rz"))
     return 3 * general > sum(1 for op in circuit.ops if op.params) - general
 

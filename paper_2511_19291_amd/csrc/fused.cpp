@@ -1,7 +1,7 @@
 // fused.cpp -- host side of the fused-block path: the fusion planner that
 // multiplies runs of gates into <= 5-qubit blocks (complex128), and
 // sv_apply_fused, which prepares each block's matrix for the MFMA or vector
-// kernel and queues one sweep per block.
+// kernel and queues sweeps of one block or of several that share a tile.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

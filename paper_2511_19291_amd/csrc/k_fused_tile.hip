@@ -15,9 +15,10 @@
 //
 // Bound: FP32 by the matrix cores (64 clocks per product: 8192 of a CU per block
 // and tile, 224 us per block at 27 qubits, where a sweep of its own takes 370 to
-// 400, bound by memory), which two workgroups per CU keep 72 % busy; BF16x3 by
-// memory. The planned 20-layer brickwork: FP32 at 27 qubits 45 blocks in 19 sweeps,
-// 18.0 -> 15.1 ms; BF16x3 at 26 qubits 45 blocks in 26 sweeps, 8.5 -> 5.5 ms.
+// 400, bound by memory), which two workgroups per CU keep 66 % busy at 2.2 GHz
+// (median of the sweeps); BF16x3 by memory. The planned 20-layer brickwork: FP32 at
+// 27 qubits 45 blocks in 19 sweeps, 18.0 -> 15.1 ms; BF16x3 at 26 qubits 45 blocks in
+// 26 sweeps (18 of two or three blocks at 0.23 ms, 8 of one at 0.19), 8.5 -> 5.5 ms.
 // What the pause between the products is was not found: both parts' operands read
 // at once, priorities or a delay that let one workgroup run ahead, tiles of 2^12
 // with three workgroups per CU (335 us a block as now), and a persistent grid with

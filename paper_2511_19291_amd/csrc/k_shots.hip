@@ -261,13 +261,15 @@ __device__ __forceinline__ double lane_prob(const float2* __restrict__ p, uint32
 // group first finds the shot's chunk of 128 amplitudes from the block's chunk
 // masses as k_block_mass stored them (lane i: chunks 4i .. 4i + 3, running
 // sums in chunk order, then across the eight lanes in a fixed order): the
-// first chunk whose running mass exceeds the shot's remainder. It then reads
-// that chunk whole (lane i: amplitudes 16i .. 16i + 15, 128 contiguous bytes)
-// and finds the first index of non-zero probability whose running sum (in
-// index order) exceeds what remains. If rounding leaves none, the last index
-// of non-zero probability in the chunk (past the last chunk: in the last
-// chunk of non-zero mass). Only the chunks that hold a shot are read, and no
-// index of zero probability is ever returned.
+// first chunk whose running mass exceeds the shot's remainder. Of that chunk it
+// forms the sums of 16 amplitudes from the whole chunk, 128 contiguous bytes a
+// load, or reads them where the mass pass kept them (SUB: the same sums, by the
+// same tree); lane i holds the i-th. In the first sub-block whose running sum
+// exceeds what remains, lane i has amplitudes 2i and 2i + 1 (SUB: one line read
+// now), and the first index of non-zero probability whose running sum (in index
+// order) exceeds the rest is the shot's. If rounding leaves none, the last index
+// of non-zero probability in the sub-block (past the last sub-block or chunk: of
+// the last of non-zero mass). No index of zero probability is ever returned.
 __device__ __forceinline__ double group_incl8(double v, int gi)
 {
     // inclusive scan over the eight lanes of a group (Hillis-Steele, fixed order)

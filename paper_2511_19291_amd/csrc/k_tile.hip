@@ -9,11 +9,11 @@
 // addresses written to.
 //
 // Bound: far beyond the caches, the vector unit. 27-qubit brickwork (540 U3 +
-// 260 CZ): 24 launches at 0.90 ms, 21.7 ms in all (one sweep per gate:
+// 260 CZ): 23 launches at 0.92 ms, 21.8 ms in all (one sweep per gate:
 // 213 ms); 16 instructions a pair and general gate are 2880 of the 4000
 // vector instructions of a wave and launch, issued at 97 % of one every four
 // cycles; HBM traffic (16 B per amplitude and launch) would take 0.33 ms of
-// each 0.90. The matrix cores (v_mfma_f32_4x4x1, one pair per lane) halve the
+// each 0.92. The matrix cores (v_mfma_f32_4x4x1, one pair per lane) halve the
 // instructions of the gates but not the time (0.92 ms a launch): their
 // results need moving back to the amplitudes' registers. Small states: the
 // latency of a step, about 0.4 us, half of it branches; a 12-qubit,

@@ -747,9 +747,9 @@ def batch_autotune(circuits: Sequence, reps: int = 3, device=None, params_list=N
 
 def fused_autotune(state: "State", circuit, modes: Sequence[int] = (FUSED_FP32_MFMA, FUSED_VALU), reps: int = 2,
                    params=None):
-    """Time the circuit on ``state`` as plain sweeps and as fused blocks of
+    """Time the circuit on ``state`` as a gate list and as fused blocks of
     each width in the allowed modes (the state is overwritten). Returns (best
-    choice dict, list of trial dicts); mode -1 means plain per-gate sweeps."""
+    choice dict, list of trial dicts); mode -1 means the gate list (``run``)."""
     table = OpTable(circuit.ops)
     p = np.ascontiguousarray(np.asarray(circuit.params if params is None else params, dtype=np.float64))
     mask = 0
