@@ -484,7 +484,7 @@ def extras(args, n, gate_by_gate_per_s, avg_dense_ms, copy_GBps) -> dict:
         if lb == sv.ADJOINT_MFMA:
             grad_mfma = grad_b[0].copy()
         blocked["mfma4" if lb == sv.ADJOINT_MFMA else f"block{lb}"] = {"backward_ms": round(ms_b, 2), "backward_over_forward": round(ms_b / fwd_ms, 3),
-                                 "max_grad_diff_vs_per_gate": float(np.max(np.abs(grad_b[0] - grad[0]))),
+                                 "max_grad_diff_vs_tiles": float(np.max(np.abs(grad_b[0] - grad[0]))),
                                  "drift": float(drift_b[0])}
     # the autograd layers' forward: row-shared gates fused into 5-qubit
     # matrix-core blocks (host planning included in the time)
@@ -525,7 +525,6 @@ def extras(args, n, gate_by_gate_per_s, avg_dense_ms, copy_GBps) -> dict:
         "backward_ms": round(default_ms, 2),
         "backward_kind": "gate by gate in tiles of state and co-state (the autograd default for one-target rotations)",
         "backward_over_forward": round(default_ms / fwd_ms, 3),
-        "backward_per_gate_ms": round(bwd_ms, 2), "per_gate_over_forward": round(bwd_ms / fwd_ms, 3),
         "param_shift": {"measured": "16 seeded parameters on this GPU, two forwards + <sum Z> each, "
                                     "scaled to all parameters", "gate_list_forward": shift["gate_list"],
                         "fused_forward": shift["fused"]},
@@ -545,7 +544,7 @@ def extras(args, n, gate_by_gate_per_s, avg_dense_ms, copy_GBps) -> dict:
         res["adjoint"]["error_vs_oracle"] = {
             "oracle": "tests/golden/ring28.json (complex128 adjoint)",
             "loss_abs": abs(float(loss[0]) - g28["loss"]),
-            "per_gate_rel_max": float(np.max(np.abs(grad[0] - want)) / np.max(np.abs(want))),
+            "tiles_rel_max": float(np.max(np.abs(grad[0] - want)) / np.max(np.abs(want))),
             "mfma4_rel_max": float(np.max(np.abs(grad_mfma - want)) / np.max(np.abs(want))),
         }
     st.free()
@@ -589,7 +588,7 @@ def extras(args, n, gate_by_gate_per_s, avg_dense_ms, copy_GBps) -> dict:
     }
     print("# profiling ladder done", file=sys.stderr, flush=True)
 
-    # -- batched: 256 uneven circuits in one graph launch vs per-gate launches;
+    # -- batched: 256 uneven circuits in one graph launch vs one by one as gate lists;
     #    the launch shape is picked by the library's autotuner
     circs = C.batch_workload(256, 10, 20, 6, 4)
     t0 = time.perf_counter()
@@ -632,9 +631,9 @@ def extras(args, n, gate_by_gate_per_s, avg_dense_ms, copy_GBps) -> dict:
 
     res["batched"] = {
         "workload": "256 circuits, n uniform in 10..20, encoded RY inputs + 6 x [RY, RZ, CNOT ladder], all <Z_i>",
-        "gates": gates, "graph_launch_ms": round(graph_ms, 3), "per_gate_launches_ms": round(pergate_ms, 2),
+        "gates": gates, "graph_launch_ms": round(graph_ms, 3), "one_by_one_ms": round(pergate_ms, 2),
         "gates_per_s": round(gates / (graph_ms / 1e3), 1),
-        "speedup_vs_per_gate": round(pergate_ms / graph_ms, 2),
+        "speedup_vs_one_by_one": round(pergate_ms / graph_ms, 2),
         "default_config_ms": round(timings["default"], 3),
         # a fused phase amplitude costs, FP32 (Gauss): three real 16-wide
         # rows = 48 multiply-adds = 96 FLOP; BF16x3: three rows of the real

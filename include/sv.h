@@ -555,8 +555,9 @@ sv_status sv_batch_param_layout(sv_batch_plan p, int64_t* param_offsets, int64_t
 #define SV_BATCH_OUT_STRIDE 32
 sv_status sv_batch_launch(sv_batch_plan p, const double* dev_params, double* dev_out);
 
-/* Same work as sv_batch_launch without the graph: one kernel launch per gate
- * per circuit (the plain per-gate form the batched launch is compared with). */
+/* Same work as sv_batch_launch without the graph: the circuits one after the
+ * other, each as a gate list (sv_run) and its <Z_i>, which the batched launch is
+ * compared with. Synchronous. */
 sv_status sv_batch_launch_pergate(sv_batch_plan p, const double* dev_params, double* dev_out);
 
 /* Testing hook for the bounded inter-pass wait of the batched launch (no
