@@ -1080,20 +1080,14 @@ void plan_pauli_tiles(int n, int rows, const uint64_t* x, const uint64_t* z, int
     // qubits of the strings' choice
     constexpr uint64_t kRun = 15;
     const int T = tile_bits(n);
-    std::vector<int> left(count);
-    for (int i = 0; i < count; ++i) left[i] = i;
+    std::vector<int> left;
+    left.reserve(count);
+    rest.clear();
+    for (int i = 0; i < count; ++i) (__builtin_popcountll(x[i] | kRun) > std::max(T, 4) ? rest : left).push_back(i);
     auto imag = [&](int i) { return __builtin_popcountll(x[i] & z[i]) & 1; };
     std::stable_sort(left.begin(), left.end(), [&](int a, int b) {
         return x[a] != x[b] ? x[a] < x[b] : imag(a) < imag(b);
     });
-    rest.clear();
-    left.erase(std::remove_if(left.begin(), left.end(),
-                              [&](int i) {
-                                  const bool wide = __builtin_popcountll(x[i] | kRun) > std::max(T, 4);
-                                  if (wide) rest.push_back(i);
-                                  return wide;
-                              }),
-               left.end());
     while (!left.empty()) {
         uint64_t S = T == n ? (1ull << n) - 1 : kRun;
         for (int i : left)

@@ -172,12 +172,14 @@ static int strings()
         // 1125 : 353; single rows of any width
         {13, 20000, 3, 3, true}, {8, 1, 2, 2, true}, {12, 1, 3, 3, true}, {24, 1, 2, 2, true},
         // one x: 21.5 : 23.3 at 8 qubits, 32.2 : 24.9 at 20
-        {8, 1, 8, 1, false}, {20, 1, 8, 1, true}};
+        {8, 1, 8, 1, false}, {20, 1, 8, 1, true},
+        // x wider than a tile
+        {16, 1, 300, 0, false}, {24, 1, 300, 0, false}};
     for (const auto& k : cases) {
         std::vector<uint64_t> x(k.count), z(k.count);
         for (int i = 0; i < k.count; ++i) {
-            x[i] = 1 + i % k.xs;
-            z[i] = i / k.xs;
+            x[i] = k.xs ? 1 + i % k.xs : (1ull << k.n) - 1 - (i % 2);
+            z[i] = k.xs ? i / k.xs : i;
         }
         std::vector<sv::PauliSweep> sweeps;
         std::vector<int> rest;
