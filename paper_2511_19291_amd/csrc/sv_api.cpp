@@ -142,10 +142,9 @@ void check_not_capturing(hipStream_t st)
 
 // ------------------------------------------------------------ scratch
 
-// false: there is no memory for it (and the scratch is gone)
-bool try_scratch(sv_state s, uint64_t doubles)
+void ensure_scratch(sv_state s, uint64_t doubles)
 {
-    if (doubles <= s->scratch_cap) return true;
+    if (doubles <= s->scratch_cap) return;
     if (s->scratch) {
         SV_HIP(hipStreamSynchronize(s->stream));
         SV_HIP(hipFree(s->scratch));
@@ -155,15 +154,28 @@ bool try_scratch(sv_state s, uint64_t doubles)
     if (hipMalloc(&s->scratch, doubles * sizeof(double)) != hipSuccess) {
         (void)hipGetLastError();
         s->scratch = nullptr;
-        return false;
+        fail(SV_ERR_OUT_OF_MEMORY, "reduction scratch allocation failed");
     }
     s->scratch_cap = doubles;
-    return true;
 }
 
-void ensure_scratch(sv_state s, uint64_t doubles)
+// Scratch that a call can do without: false if there is no memory for it beside
+// the one held, which then stays.
+bool try_scratch(sv_state s, uint64_t doubles)
 {
-    need(try_scratch(s, doubles), SV_ERR_OUT_OF_MEMORY, "reduction scratch allocation failed");
+    if (doubles <= s->scratch_cap) return true;
+    double* p = nullptr;
+    if (hipMalloc(&p, doubles * sizeof(double)) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (s->scratch) {
+        SV_HIP(hipStreamSynchronize(s->stream));
+        SV_HIP(hipFree(s->scratch));
+    }
+    s->scratch = p;
+    s->scratch_cap = doubles;
+    return true;
 }
 
 void ensure_dout(sv_state s, uint64_t doubles)

@@ -16,7 +16,7 @@ static std::map<const void*, std::string> kernel_names;
 static std::vector<std::string> launched;
 static std::map<void*, size_t> held;
 static size_t memory_limit = ~size_t(0), memory_held = 0;
-static int allocations = 0;
+static int allocations = 0, frees = 0;
 static bool capturing = false;
 static size_t configured;
 
@@ -67,6 +67,7 @@ hipError_t hipMalloc(void** p, size_t bytes)
 }
 hipError_t hipFree(void* p)
 {
+    ++frees;
     memory_held -= held[p];
     held.erase(p);
     std::free(p);

@@ -38,6 +38,8 @@ int main()
     check(memory_limit < state + draws + sums, "the limit lies below the sums");
     check(sv_alloc(n, 1, nullptr, nullptr, &s) == SV_OK, "sv_alloc");
     check(draw(s, shots) == SV_OK && was_launched(without) && !was_launched(with), "no room for the sums: without them");
+    frees = 0;
+    check(draw(s, shots) == SV_OK && was_launched(without) && frees == 0, "again: the scratch held stays");
     // held memory that is enough without them: captured, nothing is allocated
     capturing = true;
     check(draw(s, shots) == SV_OK && was_launched(without) && allocations == 0, "captured, without the sums");
