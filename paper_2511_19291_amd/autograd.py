@@ -118,7 +118,11 @@ def _blocks_pay(circuit, width: float) -> bool:
     layers). Training steps, tiles against blocks: bricks with controlled
     rotations at 24 / 25 / 27 qubits 7.4 / 14.0 / 30.6 ms against 6.7 / 10.9 /
     21.8, ladders of them 4.5 / 9.0 / 36.0 against 6.5 / 10.9 / 39.3; bricks with
-    CNOTs and a quarter of U3 3.0 / 5.5 / 23.6 against 3.9 / 6.5 / 21.7."""
+    CNOTs and a quarter of U3 3.0 / 5.5 / 23.6 against 3.9 / 6.5 / 21.7. Rows count as
+    qubits do from 21 qubits on (bricks of CRX, 16 rows of 21 qubits with angles of
+    their own 8.3 against 6.4); blocks of more rows of fewer qubits are bound by
+    the host, which forms each row's (16 rows of 20: 4.2 against 4.7, 256 of 18
+    with encoded inputs: 12.5 against 27.8)."""
     tiles, several, mixed = 0.0, 0, False
     for op in circuit.ops:
         wide = len(op.targets) + len(op.controls) > 1
@@ -144,7 +148,7 @@ def default_block_qubits(circuit, batch: int = 1) -> int:
     width = circuit.n + np.log2(max(int(batch), 1))
     if width > TILE_GENERAL_MAX_QUBITS and _mostly_general(circuit):
         return sv.ADJOINT_MFMA
-    if width > TILE_MIXED_MAX_QUBITS and _blocks_pay(circuit, width):
+    if width > TILE_MIXED_MAX_QUBITS and circuit.n > TILE_GENERAL_MAX_QUBITS and _blocks_pay(circuit, width):
         return sv.ADJOINT_MFMA
     return 0
 

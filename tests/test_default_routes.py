@@ -38,7 +38,10 @@ def _ladder(n, layers):
 @pytest.mark.parametrize("circ, batch, want", [
     # controlled rotations in bricks (tiles : blocks, ms): 14.0 : 10.9, 14.9 : 11.2, 30.6 : 21.8; 24 qubits 7.4 : 6.7
     (_bricks(25, 8, "crx", 5), 1, BLOCKS), (_bricks(26, 4, "crx", 4), 1, BLOCKS), (_bricks(27, 4, "crx", 0), 1, BLOCKS),
-    (_bricks(24, 8, "crx", 5), 1, BLOCKS), (_bricks(21, 8, "crx", 5), 16, BLOCKS),
+    (_bricks(24, 8, "crx", 5), 1, BLOCKS),
+    # in rows: 8.3 : 6.4, 14.4 : 10.5; 4.2 : 4.7 and 12.5 : 27.8 on fewer qubits
+    (_bricks(21, 8, "crx", 5), 16, BLOCKS), (_bricks(25, 8, "crx", 5), 2, BLOCKS),
+    (_bricks(20, 4, "crx", 2), 16, TILES), (_bricks(18, 4, "crx", 2), 256, TILES),
     # 3.7 : 4.5, 1.4 : 3.4 on fewer qubits
     (_bricks(23, 8, "crx", 3), 1, TILES), (_bricks(21, 8, "crx", 3), 1, TILES),
     # in ladders: 4.5 : 6.5, 9.0 : 10.9, 36.0 : 39.3
