@@ -17,7 +17,7 @@ static std::vector<std::string> launched;
 static std::map<void*, size_t> held;
 static size_t memory_limit = ~size_t(0), memory_held = 0;
 static int allocations = 0, frees = 0;
-static bool capturing = false;
+static bool capturing = false, another_captures = false;   // another: while this one is the default stream
 static size_t configured;
 
 static bool was_launched(const char* part)
@@ -86,7 +86,7 @@ hipError_t hipHostFree(void* p)
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s)
 {
     *s = capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
-    return hipSuccess;
+    return another_captures ? hipErrorStreamCaptureImplicit : hipSuccess;
 }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int)
 {

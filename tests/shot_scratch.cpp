@@ -44,6 +44,9 @@ int main()
     capturing = true;
     check(draw(s, shots) == SV_OK && was_launched(without) && allocations == 0, "captured, without the sums");
     capturing = false;
+    another_captures = true;
+    check(draw(s, shots) == SV_OK && was_launched(without) && allocations == 0, "another stream captures, without the sums");
+    another_captures = false;
     // room comes: with them, and then also captured
     memory_limit = ~size_t(0);
     check(draw(s, shots) == SV_OK && was_launched(with), "room again: with the sums");
